@@ -980,6 +980,15 @@ __global__ __launch_bounds__(kBlock) void k_scatter(SortArrays a, const DevEnv *
 
 // -------------------------------------------------------------------- sweep
 
+// m + m + (the lane's bit of mask b), one vector instruction: the lane mask of
+// a comparison enters as the carry.
+__device__ __forceinline__ uint32_t shift_in(uint32_t m, uint64_t b) {
+    uint64_t carry;
+    uint32_t r;
+    asm("v_addc_co_u32_e64 %0, %1, %2, %2, %3" : "=v"(r), "=s"(carry) : "v"(m), "s"(b));
+    return r;
+}
+
 // atan(t) / (2 pi) for t in [0, 1] as t * P(t^2); least-squares fit with
 // minimax reweighting on Chebyshev nodes, max error 5.4e-8 turns.
 __device__ __forceinline__ float atan_turns01(float t) {
@@ -1023,30 +1032,26 @@ __device__ __forceinline__ int sector_oct(float dx, float dy, float c, float s) 
     const float au = fabsf(u), aw = fabsf(w);
     // min/max > tan(edge), tested as min > tan(edge) * max (no division; a
     // coincident pair, max = 0, stays in sector 0)
-    int j = 0;
-    if constexpr (M > 1) {
-        const float mx = fmaxf(au, aw), mn = fminf(au, aw);
-        if constexpr (M == 2) {
-            j = mn > 0.41421356237309503f * mx ? 1 : 0;  // tan(pi/8)
-        } else {
-            static_assert(M == 4, "sector_oct takes M = 1, 2 or 4");
-            j = (mn > 0.19891236737965800f * mx ? 1 : 0) + (mn > 0.41421356237309503f * mx ? 1 : 0) +
-                (mn > 0.66817863791929891f * mx ? 1 : 0);  // tan(pi/16), tan(pi/8), tan(3 pi/16)
-        }
-    }
     // mirroring within [0, 2^b) is an XOR with 2^b - 1, so the three mirrors
     // (past 45 degrees, past 90, past 180) flip whole bit groups: the top bit
     // is w < 0, the next (u < 0) ^ (w < 0), the lower ones that ^ (|w| > |u|),
-    // and j's bits flip with those (kept as lane masks, combined once)
-    const bool b3 = w < 0.0f;
-    const bool b2 = b3 ^ (u < 0.0f);
-    const bool b1 = b2 ^ (aw > au);
-    if constexpr (M == 1) {
-        return (b3 ? 4 : 0) | (b2 ? 2 : 0) | (b1 ? 1 : 0);
-    } else if constexpr (M == 2) {
-        return (b3 ? 8 : 0) | (b2 ? 4 : 0) | (b1 ? 2 : 0) | ((b1 ^ (j != 0)) ? 1 : 0);
+    // and the sector within the octant flips with those.  The bits are kept as
+    // lane masks (scalar XORs) and shifted in from the top.
+    const uint64_t b3 = __ballot(w < 0.0f);
+    const uint64_t b2 = b3 ^ __ballot(u < 0.0f);
+    const uint64_t b1 = b2 ^ __ballot(aw > au);
+    const uint32_t oct = shift_in(shift_in(shift_in(0u, b3), b2), b1);
+    if constexpr (M == 1) return (int)oct;
+    const float mx = fmaxf(au, aw), mn = fminf(au, aw);
+    if constexpr (M == 2) {
+        return (int)shift_in(oct, b1 ^ __ballot(mn > 0.41421356237309503f * mx));  // tan(pi/8)
     } else {
-        return (b3 ? 16 : 0) | (b2 ? 8 : 0) | (b1 ? 4 : 0) | (j ^ (b1 ? 3 : 0));
+        static_assert(M == 1 || M == 4, "sector_oct takes M = 1, 2 or 4");
+        // j = 0 .. 3 edges passed: tan(pi/16), tan(pi/8), tan(3 pi/16)
+        const uint64_t e1 = __ballot(mn > 0.19891236737965800f * mx);
+        const uint64_t e2 = __ballot(mn > 0.41421356237309503f * mx);
+        const uint64_t e3 = __ballot(mn > 0.66817863791929891f * mx);
+        return (int)shift_in(shift_in(oct, b1 ^ e2), b1 ^ (e1 ^ e2 ^ e3));
     }
 }
 
@@ -1094,8 +1099,7 @@ struct ViewK {
 // neighbour the count, the collision count and the per-sector minimum (an
 // LDS atomic min on the agent's own minima, S words apart).  The sector is
 // computed for every candidate (branch-free); only the LDS update is
-// predicated.  With G lanes per agent, lane li takes candidates q + li,
-// q + li + G, ...  (offx, xi), (offy, yi): candidate shift (0 or -L) and
+// predicated.  (offx, xi), (offy, yi): candidate shift (0 or -L) and
 // centre (x or x - L) per axis; minimg selects the per-candidate minimum
 // image (single-cell envs).  kFov selects the limited-view sector
 // (candidates outside the arc are counted but update no sector).
@@ -1149,25 +1153,27 @@ __device__ __forceinline__ void test_pair(uint32_t *smin_own, const uint8_t *__r
     }
 }
 
-template <int S, int G, int UNROLL, bool kFov, bool kTag, int kM, bool kShiftX, bool kShiftY>
+// Candidates per step of a run walked on its own (one lane per agent, stencil
+// half-width 2 or a single cell).
+constexpr int kRunUnroll = 4;
+
+template <int S, bool kFov, bool kTag, int kM, bool kShiftX, bool kShiftY>
 __device__ __forceinline__ void sweep_run(uint32_t *smin_own, const float2 *__restrict__ sxy,
                                           const uint8_t *__restrict__ stype, int ti,
-                                          int q, int q1, int li, int self, float offx, float xi,
+                                          int q, int q1, int self, float offx, float xi,
                                           float offy, float yi, bool minimg, float L, float r2,
                                           float c2, const ViewK &K, int &nb, int &col) {
-    auto test = [&](const float2 pj, int qq, bool valid) {
-        test_pair<S, kFov, kTag, kM, kShiftX, kShiftY>(smin_own, stype, ti, pj, qq,
-                                                       valid && qq != self, offx, xi, offy, yi,
-                                                       minimg, L, r2, c2, K, nb, col);
-    };
-    // UNROLL candidates per lane and step, those past the run's end masked
-    // (the position arrays are padded for the reads)
-    for (q += li; q < q1; q += UNROLL * G) {
-        float2 pj[UNROLL];
+    // kRunUnroll candidates per step, those past the run's end masked (the
+    // position arrays are padded for the reads)
+    for (; q < q1; q += kRunUnroll) {
+        float2 pj[kRunUnroll];
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) pj[u] = sxy[q + u * G];
+        for (int u = 0; u < kRunUnroll; ++u) pj[u] = sxy[q + u];
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) test(pj[u], q + u * G, q + u * G < q1);
+        for (int u = 0; u < kRunUnroll; ++u)
+            test_pair<S, kFov, kTag, kM, kShiftX, kShiftY>(smin_own, stype, ti, pj[u], q + u,
+                                                           q + u < q1 && q + u != self, offx, xi,
+                                                           offy, yi, minimg, L, r2, c2, K, nb, col);
     }
 }
 
@@ -1204,14 +1210,6 @@ __device__ __forceinline__ bool column_rows(const RowGeom &E, float fx, int ox, 
     return true;
 }
 
-// Candidates per lane and loop step of a lane group's run (independent loads
-// in flight): groups of 16 or 64 lanes split a run into short pieces, where
-// masked slots past its end cost more than fewer loads in flight (MI355X,
-// 128-sector flock at 16 lanes: 209 us at 4, 193 at 2; 4 lanes: 242 at 4,
-// 248 at 2).
-template <int G>
-constexpr int unroll_for() { return G >= 16 ? 2 : 4; }
-constexpr int kUnrollMax = 4;
 // One lane per agent, stencil half-width 1: walk the agent's runs as one
 // sequence (a lane moves to its next run as soon as its current one ends)
 // instead of run by run, so a wave waits for its longest total rather than
@@ -1222,13 +1220,16 @@ constexpr bool kFlatRuns = true;
 // Candidates per step of the flat walk; step of 200 x 5,000 agents, 16 sectors:
 // 4 -> 70.1 us, 5 -> 71.0, 6 -> 70.6, 8 -> 73.2.
 constexpr int kFlatUnroll = 4;
+// Candidates per lane and step of a lane group's run (four lanes without the
+// queue: 4).
+constexpr int kGroupUnroll = 2;
 // Entries past the end of the cell-order position and type arrays, so that a
 // step's reads past the last run stay inside the allocation: a lane reads at
-// most (unroll - 1) * G + G - 1 < kUnrollMax * 64 (lane groups of G <= 64)
-// or kFlatUnroll - 1 entries past its run's end.
+// most kGroupUnroll * G - 1 entries (lane groups of G <= 64) or kFlatUnroll - 1
+// entries past its run's end.
 constexpr int kSortPad = 256;
-static_assert(unroll_for<4>() <= kUnrollMax && unroll_for<64>() <= kUnrollMax, "unroll bound");
-static_assert(kFlatUnroll <= kSortPad + 1 && kUnrollMax * 64 <= kSortPad + 1,
+static_assert(kFlatUnroll <= kSortPad + 1 && kRunUnroll <= kSortPad + 1 && 4 * 4 <= kSortPad + 1 &&
+                  kGroupUnroll * 64 <= kSortPad + 1,
               "pad the cell-order arrays for the unrolled reads");
 
 // The runs of one agent's flat walk (one lane per agent, one column either
@@ -1282,6 +1283,232 @@ __device__ __forceinline__ void flat_runs(const RowGeom &RG, const int32_t *__re
     F.nr = nr;
 }
 
+// ---- lane groups: G lanes share an agent, 64 / G agents to a wave
+//
+// A wave's neighbours pass through a queue in LDS.  Distance tests (some ten
+// vector instructions per candidate) push the displacement of each candidate
+// in range, and its agent's place in the wave; whenever 64 are queued, each
+// lane takes one and evaluates its bearing, sector and minimum (30 to 50
+// instructions), for whichever agent it belongs to.  Testing and seeing in
+// one pass paid the bearing for every candidate slot, since some lane of a
+// wave has a neighbour on nearly each of them.  Bound by vector-ALU issue
+// (10,000 agents, 128 sectors, 250 degrees, 64 lanes: 998 -> 671 wave
+// instructions per agent; the launch 22.8 -> 17.7 us, 16,000 agents at reach
+// two 36.6 -> 28.9 us).
+constexpr int kQueue = 63 + 64 * kGroupUnroll + 1;  // entries: a rest below 64, one step's pushes
+
+// Whether a lane group's sweep queues its neighbours: views whose sector takes
+// the arctangent, and steps of 64 lanes.  Sectors by octant (kM > 0) cost
+// about what a push and a pop do, so where most candidates are neighbours they
+// are evaluated in place (20 x 50,000 clustered agents at four lanes: 266 us
+// per step against 309 queued, 282 before); with 64 lanes few lanes of a slot
+// have one (one 5,000-agent env: 16.7 us per step against 17.7 in place).
+__host__ __device__ constexpr bool queued(int G, int kM) { return kM == 0 || G == 64; }
+
+// 32-bit words of LDS per wave.
+__host__ __device__ constexpr int queue_words(int G, int kM) {
+    return queued(G, kM) ? (3 * kQueue + 3 * (64 / G) + 3) & ~3 : 0;
+}
+
+struct WaveQueue {
+    float *x, *y;    // [kQueue] displacement of a neighbour from its agent
+    uint32_t *meta;  // [kQueue] agent of the entry; tag: + 64 type, + 128 types differ
+    float2 *cs;      // [64 / G] cos / sin of the agents' headings
+    int *col;        // [64 / G] collisions (tag: touches)
+};
+
+template <int G>
+__device__ __forceinline__ WaveQueue wave_queue(uint32_t *words) {
+    WaveQueue Q;
+    Q.x = reinterpret_cast<float *>(words);
+    Q.y = Q.x + kQueue;
+    Q.meta = words + 2 * kQueue;
+    Q.cs = reinterpret_cast<float2 *>(words + 3 * kQueue);
+    Q.col = reinterpret_cast<int *>(Q.cs + 64 / G);
+    return Q;
+}
+
+// n + (the lane's bit of mask b) in one vector instruction.
+__device__ __forceinline__ int add_bit(int n, uint64_t b) {
+    uint64_t carry;
+    int r;
+    asm("v_addc_co_u32_e64 %0, %1, 0, %2, %3" : "=v"(r), "=s"(carry) : "v"(n), "s"(b));
+    return r;
+}
+
+// The candidates of the wave's agents in env E: neighbours per lane into nb
+// (tag: runners), minima and collision counts in LDS.  mine: the lane's agent
+// exists and lives in E; every lane of the wave takes part.  smin_w: minima of
+// the wave's first agent (agent i's i words on).
+template <int A, int G, bool kFov, bool kTag, int kM>
+__device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E, uint32_t *smin_w,
+                                            const WaveQueue &Q, bool mine, float4 me, int pos,
+                                            int ti, const ViewK &K, int &nb, int &col) {
+    const int lane = threadIdx.x & 63, li = lane % G, own = lane / G;
+    const float L = E.box, r2 = E.r2, c2 = E.c2;
+    const int ncx = E.ncx, ncy = E.ncy, cb = E.cell_base, reach = E.reach;
+    constexpr bool kQueued = queued(G, kM);
+    int cnt = 0;  // queued entries (wave-uniform)
+
+    // the last n (at most 64) entries, one per lane
+    auto drain = [&](int n) {
+        cnt -= n;
+        wave_lds_fence();
+        if (lane < n) {
+            const float2 d = make_float2(Q.x[cnt + lane], Q.y[cnt + lane]);
+            int o = 0, meta = 0;
+            if constexpr (G < 64 || kTag) {
+                meta = (int)Q.meta[cnt + lane];
+                o = kTag ? meta & 63 : meta;
+            }
+            const float2 cs = G < 64 ? Q.cs[o] : make_float2(K.c, K.s);
+            const float d2 = __builtin_fmaf(d.x, d.x, d.y * d.y);
+            int ch = 0;
+            if constexpr (kTag) ch = (meta & 64) ? K.v : 0;
+            int k;
+            if constexpr (kFov)
+                k = view_sector(d.x, d.y, cs.x, cs.y, K.fov_half, K.fov_t, K.sec_scale, K.v);
+            else if constexpr (kM > 0) k = sector_oct<kM>(d.x, d.y, cs.x, cs.y);
+            else k = sector_of(d.x, d.y, cs.x, cs.y, K.vf, K.v);
+            if (!kFov || k >= 0) atomicMin(&smin_w[(ch + k) * A + o], __float_as_uint(d2));
+            if (d2 < c2 && (!kTag || (meta & 128))) atomicAdd(&Q.col[o], 1);
+        }
+        wave_lds_fence();
+    };
+    // candidates [q, q + len) of the lane's group (lane li takes every G-th);
+    // kMode 1: candidate shifts (offx, offy), centres (xi, yi); 2: minimum
+    // image; kSelf: the agent itself may be among them
+    auto run = [&](auto kmode, auto kself, int q, int len, float offx, float xi, float offy,
+                   float yi) {
+        constexpr int kMode = decltype(kmode)::value;
+        if constexpr (!kQueued) {
+            constexpr int U = G == 4 ? 4 : kGroupUnroll;
+            for (int t = li; t < len; t += U * G) {
+                float2 p[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) p[u] = a.sxy[q + t + u * G];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    bool ok = t + u * G < len;
+                    if constexpr (decltype(kself)::value) ok = ok && q + t + u * G != pos;
+                    test_pair<A, kFov, kTag, kM, kMode == 1, kMode == 1>(
+                        smin_w + own, a.stype, ti, p[u], q + t + u * G, ok, offx,
+                        kMode == 1 ? xi : me.x, offy, kMode == 1 ? yi : me.y, kMode == 2, L, r2,
+                        c2, K, nb, col);
+                }
+            }
+            return;
+        }
+        for (int t = li; __any(t < len); t += kGroupUnroll * G) {
+            const int at = G < 64 && t >= len ? q : q + t;
+            float2 p[kGroupUnroll];
+            int tj[kGroupUnroll];
+#pragma unroll
+            for (int u = 0; u < kGroupUnroll; ++u) {
+                p[u] = a.sxy[at + u * G];
+                if constexpr (kTag) tj[u] = a.stype[at + u * G];
+            }
+#pragma unroll
+            for (int u = 0; u < kGroupUnroll; ++u) {
+                float dx, dy;
+                if constexpr (kMode == 0) {
+                    dx = p[u].x - me.x;
+                    dy = p[u].y - me.y;
+                } else if constexpr (kMode == 1) {
+                    dx = (p[u].x + offx) - xi;
+                    dy = (p[u].y + offy) - yi;
+                } else {
+                    dx = min_image_delta(p[u].x, me.x, L);
+                    dy = min_image_delta(p[u].y, me.y, L);
+                }
+                // lane masks (combined by scalar instructions)
+                uint64_t b = __ballot(__builtin_fmaf(dx, dx, dy * dy) < r2) &
+                             __ballot(t + u * G < len);
+                if constexpr (decltype(kself)::value) b &= ~__ballot(q + t + u * G == pos);
+                if (b == 0) continue;
+                const int n = __popcll(b);
+                if constexpr (kTag) nb = add_bit(nb, b & __ballot(tj[u] == 0));
+                else if constexpr (G < 64) nb = add_bit(nb, b);
+                else nb += n;
+                const uint32_t k = __builtin_amdgcn_mbcnt_hi(
+                    (uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+                if (__builtin_amdgcn_inverse_ballot_w64(b)) {
+                    (Q.x + cnt)[k] = dx;
+                    (Q.y + cnt)[k] = dy;
+                    if constexpr (kTag)
+                        (Q.meta + cnt)[k] = (uint32_t)(own | (tj[u] ? 64 : 0) | (tj[u] != ti ? 128 : 0));
+                    else if constexpr (G < 64) (Q.meta + cnt)[k] = (uint32_t)own;
+                }
+                cnt += n;
+            }
+            while (cnt >= 64) drain(64);
+        }
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
+    using Plain = std::integral_constant<int, 0>;
+    using Shift = std::integral_constant<int, 1>;
+    using Image = std::integral_constant<int, 2>;
+
+    if (ncx == 1) {
+        run(Image{}, Yes{}, a.start[cb], mine ? a.start[cb + 1] - a.start[cb] : 0, 0.0f, 0.0f, 0.0f, 0.0f);
+    } else {
+        const int cx = cell_of(me.x, E.inv_cx, ncx);
+        const float fx = me.x - (float)cx * E.cw;  // offset within the own column
+        const RowGeom RG{E.cw, E.marg, r2, E.inv_cy, ncy};
+        const int nc = 2 * reach + 1;
+        // lane li plans column li (four lanes: and column 4 + li): run A, its
+        // rows inside the column, and run B, those that wrap through the
+        // column's ends (as [q, q + l) in cell order)
+        constexpr int kSets = G < 5 ? 2 : 1;
+        int qa[kSets], la[kSets], qb[kSets], lb[kSets];
+#pragma unroll
+        for (int r = 0; r < kSets; ++r) {
+            const int c = min(li + r * G, nc - 1), ox = c - reach;
+            int lo = 0, hi = -1;
+            const bool any = column_rows(RG, fx, ox, me.y, lo, hi);
+            int ccx = cx + ox;
+            ccx = ccx < 0 ? ccx + ncx : (ccx >= ncx ? ccx - ncx : ccx);
+            const int colb = cb + ccx * ncy;
+            const int i0 = min(max(lo, 0), ncy), i1 = min(max(hi + 1, i0), ncy);
+            const int j0 = lo < 0 ? lo + ncy : 0, j1 = lo < 0 ? ncy : max(hi + 1 - ncy, 0);
+            qa[r] = a.start[colb + i0];
+            la[r] = a.start[colb + i1] - qa[r];
+            qb[r] = lb[r] = 0;
+            if (j1 > j0) {
+                qb[r] = a.start[colb + j0];
+                lb[r] = a.start[colb + j1] - qb[r];
+            }
+            if (!mine || !any) la[r] = lb[r] = 0;
+        }
+        const bool wraps = __any(lb[0] > 0 || lb[kSets - 1] > 0);
+        // a column left of column 0 wraps to the right edge with its candidates
+        // shifted by -L, one right of the last to the left edge with the centre
+        // shifted instead; rows wrap likewise (only near one end: 2 R < L)
+        const bool low = me.y < 0.5f * L;
+        const float oyb = low ? -L : 0.0f, yb = low ? me.y : me.y - L;
+        for (int c = 0; c < nc; ++c) {
+            const int r = kSets > 1 && c >= G ? 1 : 0;
+            auto of = [&](const int (&x)[kSets]) {
+                const int v = kSets > 1 && r ? x[kSets - 1] : x[0];
+                if constexpr (G == 64) return __builtin_amdgcn_readlane(v, c);
+                else return __shfl(v, (lane & ~(G - 1)) + c - r * G, 64);
+            };
+            const int ccx = cx + c - reach;
+            const float offx = ccx < 0 ? -L : 0.0f, xi = ccx >= ncx ? me.x - L : me.x;
+            const int q = of(qa), l = of(la);
+            if (__any(ccx < 0 || ccx >= ncx)) run(Shift{}, Yes{}, q, l, offx, xi, 0.0f, me.y);
+            else if (c == reach) run(Plain{}, Yes{}, q, l, 0.0f, 0.0f, 0.0f, 0.0f);
+            else run(Plain{}, No{}, q, l, 0.0f, 0.0f, 0.0f, 0.0f);
+            if (wraps) {
+                const int w = of(lb);
+                if (__any(w > 0)) run(Shift{}, Yes{}, of(qb), w, offx, xi, oyb, yb);
+            }
+        }
+    }
+    if (kQueued && cnt > 0) drain(cnt);
+}
+
 // NT threads per block, G lanes per agent (in the new cell order): A = NT/G
 // agents per block, their sector minima v * A * 4 bytes of dynamic LDS.  G = 1
 // suits sparse neighbourhoods (a few dozen candidates); dense ones (hundreds
@@ -1320,6 +1547,13 @@ __host__ __device__ constexpr SweepPolLds sweep_pol_lds(int min_words, int A, in
     return SweepPolLds{pc, speed, env, id, hid, hid + (alias ? 0 : (NT / 64) * 16 * kHidLd / 2)};
 }
 
+// 32-bit words of LDS of a sweep block before the policy's: the minima, then
+// (lane groups) each wave's queue.
+__host__ __device__ constexpr int sweep_words(int vs, int NT, int G, int kM) {
+    const int minima = vs * (NT / G);
+    return G == 1 ? minima : ((minima + 3) & ~3) + NT / 64 * queue_words(G, kM);
+}
+
 template <int NT, int G, bool kFov, bool kTag, int kM, int kPol = 0>
 __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__restrict__ envs,
                                               int n_envs, int Gtot, int v, int obs_dim,
@@ -1327,18 +1561,19 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
                                               int add_ret, PolFuse pf) {
     static_assert(kPol == 0 || !kTag, "the fused policy serves flock envs");
     constexpr int A = NT / G;
-    extern __shared__ uint32_t s_min[];  // [channels * v][A] (then the policy's, kPol)
+    extern __shared__ uint32_t s_min[];  // [channels * v][A], the queues, the policy's (kPol)
     const int vs = kTag ? 2 * v : v;     // minima per agent
     __shared__ int s_env;
     __shared__ float *s_orow[G == 1 && kPol == 0 ? NT : 1];  // view rows (one lane per agent)
     const int tid = threadIdx.x, slot = tid / G, li = tid % G;
     const int p0 = blockIdx.x * A;
-    block_env(&s_env, a.base, n_envs, p0);
+    if constexpr (G == 1) block_env(&s_env, a.base, n_envs, p0);
     uint32_t *smin = s_min + slot;
     if constexpr (G > 1)
         for (int k = li; k < vs; k += G) smin[k * A] = kInfBits;
     static_assert(kPol == 0 || G <= 4, "the fused policy needs blocks of at least 64 agents");
-    const SweepPolLds PL = sweep_pol_lds(vs * A, A, NT, G, sweep_pol_alias(G, pf.kc, vs));
+    const SweepPolLds PL =
+        sweep_pol_lds(sweep_words(vs, NT, G, kM), A, NT, G, sweep_pol_alias(G, pf.kc, vs));
     PolConsts *s_pc = reinterpret_cast<PolConsts *>(s_min + PL.pc);
     float *s_speed = reinterpret_cast<float *>(s_min + PL.speed);
     int *s_pe = reinterpret_cast<int *>(s_min + PL.env);
@@ -1347,38 +1582,83 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
     // the strip sort's look-back words and ticket, zero again for the next step
     if (blockIdx.x == 0)
         for (int i = tid; i < a.n_status; i += NT) a.status[i] = 0u;
-    __syncthreads();
+    if constexpr (G == 1 || kPol != 0) __syncthreads();
     const int pos = p0 + slot;
     if constexpr (G == 1 && kPol == 0) {
         if (pos >= Gtot) return;
     }
-    // G > 1: every lane reaches the second barrier; a group is active or not as a whole
+    // a group is active or not as a whole
     const bool active = pos < Gtot;
-    int e = s_env;
-    if (active)
+    int e = 0;
+    if constexpr (G == 1) {
+        e = s_env;
+    } else if (n_envs > 1) {
+        // lane groups: each wave finds the env of its first agent itself
+        e = wave_env_search(a.base, n_envs, min(p0 + (tid >> 6) * (64 / G), Gtot - 1));
+    }
+    if (active && (G == 1 || n_envs > 1))
         while (a.base[e + 1] <= pos) ++e;
     const DevEnv &E = envs[e];
     const int j = pos - E.agent_base;
     float4 me = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     int nb = 0, col = 0, ti = 0, my_id = 0;
-    if (active) {
-        me = load_as<(G > 1)>(E.rec_nxt, j);
+    double ret0 = 0.0;
+    if (G > 1 && active) {
+        // everything the agent needs from its env, loaded at once
+        me = gload(E.rec_nxt, j);
+        my_id = gload(E.id_nxt, j);
+        if (add_ret) ret0 = gload(E.ret_nxt, j);
+    }
+    if constexpr (G > 1) {
+        const int lane = tid & 63;
+        const WaveQueue Q = wave_queue<G>(s_min + ((vs * A + 3) & ~3) + (tid >> 6) * queue_words(G, kM));
+        const float2 cs = heading_cs(me.z);
+        if (queued(G, kM) && li == 0) {
+            Q.cs[lane / G] = cs;
+            Q.col[lane / G] = 0;
+        }
+        // env by env (few waves hold agents of more than one), so that the
+        // descriptor is wave-uniform: scalar loads and registers
+        for (uint64_t todo = __ballot(active); todo != 0;) {
+            const int e0 = __builtin_amdgcn_readlane(e, __builtin_ctzll(todo));
+            const bool mine = active && e == e0;
+            todo &= ~__ballot(mine);
+            int eu = e0;
+            asm("" : "+s"(eu));  // (else the compiler takes the lane's own equal e)
+            const DevEnv &U = envs[eu];
+            const ViewK K{cs.x, cs.y, U.fov_half, U.fov_t, U.sec_scale, (float)v, v};
+            if (kTag && mine) ti = my_id < U.n_chasers ? 1 : 0;
+            sweep_group<A, G, kFov, kTag, kM>(a, U, s_min + (tid >> 6) * (64 / G), Q, mine, me, pos,
+                                              ti, K, nb, col);
+        }
+        if constexpr (queued(G, kM)) {
+            col = Q.col[lane / G];
+#pragma unroll  // (64 lanes: nb is the whole group's already)
+            for (int m = (G < 64 || kTag) ? G / 2 : 0; m >= 1; m >>= 1) nb += __shfl_xor(nb, m, 64);
+        } else {
+            wave_lds_fence();  // the group's minima are complete
+#pragma unroll
+            for (int m = G / 2; m >= 1; m >>= 1) {
+                nb += __shfl_xor(nb, m, 64);
+                col += __shfl_xor(col, m, 64);
+            }
+        }
+    } else if (active) {
+        me = E.rec_nxt[j];
         const float2 cs = heading_cs(me.z);
         const float c = cs.x, s = cs.y;
-        if constexpr (G == 1)
-            for (int k = 0; k < vs; ++k) smin[k * A] = kInfBits;
+        for (int k = 0; k < vs; ++k) smin[k * A] = kInfBits;
 
         const ViewK K{c, s, E.fov_half, E.fov_t, E.sec_scale, (float)v, v};
-        ti = kTag ? (load_as<(G > 1)>(E.id_nxt, j) < E.n_chasers ? 1 : 0) : 0;
+        ti = kTag ? (E.id_nxt[j] < E.n_chasers ? 1 : 0) : 0;
         const float L = E.box, r2 = E.r2, c2 = E.c2;
         const int ncx = E.ncx, ncy = E.ncy, cb = E.cell_base;
         // one run of candidates [q, q1): template flags say which shifts are nonzero
         auto run = [&](auto sx, auto sy, int q, int q1, float offx, float xi, float offy, float yi,
                        bool minimg) {
-            sweep_run<A, G, unroll_for<G>(), kFov, kTag, kM, decltype(sx)::value,
-                      decltype(sy)::value>(
-                smin, a.sxy, a.stype, ti, q, q1, li, pos, offx, xi, offy, yi, minimg, L, r2, c2, K,
-                nb, col);
+            sweep_run<A, kFov, kTag, kM, decltype(sx)::value, decltype(sy)::value>(
+                smin, a.sxy, a.stype, ti, q, q1, pos, offx, xi, offy, yi, minimg, L, r2, c2, K, nb,
+                col);
         };
         using No = std::false_type;
         using Yes = std::true_type;
@@ -1389,10 +1669,6 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
             const int cx = cell_of(me.x, E.inv_cx, ncx);
             const float fx = me.x - (float)cx * E.cw;  // offset within the own column
             const RowGeom RG{E.cw, E.marg, r2, E.inv_cy, ncy};  // held in registers
-            // the column's runs over rows [lo, hi]; a column left of column 0
-            // wraps to the right edge with its candidates shifted by -L (sx),
-            // one right of the last wraps to the left edge with the centre
-            // shifted instead; rows wrap likewise
             // the column's runs over rows [lo, hi]; a column left of column 0
             // wraps to the right edge with its candidates shifted by -L (sx),
             // one right of the last wraps to the left edge with the centre
@@ -1412,45 +1688,7 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
                         false);
                 }
             };
-            // The same from the column's four cell starts st, loaded beforehand.
-            auto column = [&](auto sx, float offx, float xi, int lo, int hi, const int (&st)[4]) {
-                if (lo < 0) {
-                    run(sx, Yes{}, st[0], st[1], offx, xi, -L, me.y, false);
-                    run(sx, No{}, st[2], st[3], offx, xi, 0.0f, me.y, false);
-                } else if (hi >= ncy) {
-                    run(sx, No{}, st[0], st[1], offx, xi, 0.0f, me.y, false);
-                    run(sx, No{}, st[2], st[3], offx, xi, 0.0f, me.y - L, false);
-                } else {
-                    run(sx, No{}, st[0], st[1], offx, xi, 0.0f, me.y, false);
-                }
-            };
-            // Column ox's rows and its starts: the two runs' bounds (the second
-            // empty when rows do not wrap); false when no row is within reach.
-            // A column left of column 0 wraps to the right edge with its
-            // candidates shifted by -L, one right of the last to the left edge
-            // with the centre shifted instead.
-            auto plan_column = [&](int ox, int &lo, int &hi, int (&st)[4]) {
-                const bool any = column_rows(RG, fx, ox, me.y, lo, hi);
-                int ccx = cx + ox;
-                ccx = ccx < 0 ? ccx + ncx : (ccx >= ncx ? ccx - ncx : ccx);
-                const int colb = cb + ccx * ncy;
-                int i0 = colb + lo, i1 = colb + hi + 1, i2 = colb, i3 = colb;
-                if (lo < 0) {
-                    i0 = colb + lo + ncy;
-                    i1 = colb + ncy;
-                    i3 = colb + hi + 1;
-                } else if (hi >= ncy) {
-                    i1 = colb + ncy;
-                    i3 = colb + hi - ncy + 1;
-                }
-                if (!any) i0 = i1 = i2 = i3 = colb;
-                st[0] = a.start[i0];
-                st[1] = a.start[i1];
-                st[2] = a.start[i2];
-                st[3] = a.start[i3];
-                return any;
-            };
-            if (G == 1 && kFlatRuns && reach == 1) {
+            if (kFlatRuns && reach == 1) {
                 FlatRuns F;
                 flat_runs(RG, a.start, cb, ncx, cx, fx, me.y, F);
                 // the current run [q, q1) and its shifts; the rest queue in F
@@ -1510,12 +1748,7 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
 #pragma unroll
                     for (int u = 0; u < kFlatUnroll; ++u) pj[u] = pn[u];
                 }
-            } else if constexpr (kFov || kTag || kPol != 0) {
-                // (the limited-view and tag sweeps, whose runs are long: loading
-                // the next column's starts ahead measured no faster there, 56.0
-                // against 56.5 us per step of 16,000 agents at 128 sectors and
-                // 64 lanes, and takes 6 to 7 more registers, as it would in the
-                // policy sweeps, which already hold more than 64)
+            } else {
                 for (int ox = -reach; ox <= reach; ++ox) {
                     int lo, hi;
                     if (!column_rows(RG, fx, ox, me.y, lo, hi)) continue;
@@ -1524,40 +1757,12 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
                     else if (ccx >= ncx) column_at(No{}, cb + (ccx - ncx) * ncy, 0.0f, me.x - L, lo, hi);
                     else column_at(No{}, cb + ccx * ncy, 0.0f, me.x, lo, hi);
                 }
-            } else {
-                // each column's starts are loaded while the column before it
-                // is swept, so a lane group does not wait for them between runs
-                // (4 lanes, 20 x 50,000 clustered agents: 151 -> 143 us per
-                // step; 16 lanes, uniform: 291 -> 268)
-                int lo = 0, hi = -1, st[4];
-                bool any = plan_column(-reach, lo, hi, st);
-                for (int ox = -reach; ox <= reach; ++ox) {
-                    int nlo = 0, nhi = -1, nst[4] = {0, 0, 0, 0};
-                    const bool nany = ox < reach && plan_column(ox + 1, nlo, nhi, nst);
-                    if (any) {
-                        const int ccx = cx + ox;
-                        if (ccx < 0) column(Yes{}, -L, me.x, lo, hi, st);
-                        else if (ccx >= ncx) column(No{}, 0.0f, me.x - L, lo, hi, st);
-                        else column(No{}, 0.0f, me.x, lo, hi, st);
-                    }
-                    any = nany;
-                    lo = nlo;
-                    hi = nhi;
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) st[k] = nst[k];
-                }
             }
         }
     }  // active
 
     if constexpr (G > 1) {
-        __syncthreads();  // the group's minima are complete
         if (kPol == 0 && !active) return;
-#pragma unroll
-        for (int m = G / 2; m >= 1; m >>= 1) {
-            nb += __shfl_xor(nb, m, 64);
-            col += __shfl_xor(col, m, 64);
-        }
     }
     constexpr bool kGl = G > 1;
     // A view value from a sector minimum; with kPol it also replaces the minimum in LDS.
@@ -1575,7 +1780,7 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
     if (active) {
         // agent-order rows are addressed by id: an id out of range (a sort
         // that went wrong) writes agent 0's rows instead of outside them
-        const int id0 = load_as<kGl>(E.id_nxt, j);
+        const int id0 = G > 1 ? my_id : E.id_nxt[j];
         const int id = (unsigned)id0 < (unsigned)E.n ? id0 : 0;
         my_id = id;
         const float inv_r = E.inv_radius;
@@ -1602,7 +1807,7 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
                 (kTag && ti) ? E.r_catch * (float)col : E.r_nb * (float)nb + E.r_col * (float)col;
             if (reward) reward[E.agent_base + id] = r;
             else if (E.rew) store_as<kGl>(E.rew, id, r);
-            if (add_ret) store_as<kGl>(E.ret_nxt, j, load_as<kGl>(E.ret_nxt, j) + (double)r);
+            if (add_ret) store_as<kGl>(E.ret_nxt, j, (G > 1 ? ret0 : E.ret_nxt[j]) + (double)r);
             if (E.nb) {
                 store_as<kGl>(E.nb, id, nb);
                 store_as<kGl>(E.col, id, col);
@@ -1943,7 +2148,7 @@ template <int NT, int G, bool kFov, bool kTag, int kM = 0, int kPol = 0>
 void launch_sweep_v(const StepPlan &p, const DevEnv *envs, int Gtot, float *obs, float *reward,
                     int add_return, hipStream_t s, const PolFuse *pf) {
     constexpr int A = NT / G;
-    const int vs = (kTag ? 2 : 1) * p.v, min_words = vs * A;
+    const int vs = (kTag ? 2 : 1) * p.v, min_words = sweep_words(vs, NT, G, kM);
     const size_t lds =
         (size_t)(kPol ? sweep_pol_lds(min_words, A, NT, G, sweep_pol_alias(G, pf->kc, vs)).words
                       : min_words) *
