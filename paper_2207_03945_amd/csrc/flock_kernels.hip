@@ -980,15 +980,6 @@ __global__ __launch_bounds__(kBlock) void k_scatter(SortArrays a, const DevEnv *
 
 // -------------------------------------------------------------------- sweep
 
-// m + m + (the lane's bit of mask b), one vector instruction: the lane mask of
-// a comparison enters as the carry.
-__device__ __forceinline__ uint32_t shift_in(uint32_t m, uint64_t b) {
-    uint64_t carry;
-    uint32_t r;
-    asm("v_addc_co_u32_e64 %0, %1, %2, %2, %3" : "=v"(r), "=s"(carry) : "v"(m), "s"(b));
-    return r;
-}
-
 // atan(t) / (2 pi) for t in [0, 1] as t * P(t^2); least-squares fit with
 // minimax reweighting on Chebyshev nodes, max error 5.4e-8 turns.
 __device__ __forceinline__ float atan_turns01(float t) {
@@ -1025,33 +1016,39 @@ __device__ __forceinline__ int sector_of(float dx, float dy, float c, float s, f
 // tangents of the octant's interior sector edges, and mirrored octants
 // count their sectors backwards.  A bearing exactly on an octant edge may
 // land in either neighbouring sector (both are within the ambiguity band).
+//
+// Comparisons, selections and minima issue at half the rate of FP32 additions,
+// multiplications and bitwise operations on gfx950 (0.9 against 1.7 wave
+// instructions per clock per CU, measured), so the conditions are the sign
+// bits of differences (exact in sign; + 0 turns a -0 into +0).
 template <int M>
 __device__ __forceinline__ int sector_oct(float dx, float dy, float c, float s) {
-    const float u = __builtin_fmaf(dx, c, dy * s);
-    const float w = __builtin_fmaf(dy, c, -(dx * s));
-    const float au = fabsf(u), aw = fabsf(w);
-    // min/max > tan(edge), tested as min > tan(edge) * max (no division; a
-    // coincident pair, max = 0, stays in sector 0)
+    const float u = __builtin_fmaf(dx, c, dy * s) + 0.0f;
+    const float w = __builtin_fmaf(dy, c, -(dx * s)) + 0.0f;
     // mirroring within [0, 2^b) is an XOR with 2^b - 1, so the three mirrors
     // (past 45 degrees, past 90, past 180) flip whole bit groups: the top bit
     // is w < 0, the next (u < 0) ^ (w < 0), the lower ones that ^ (|w| > |u|),
-    // and the sector within the octant flips with those.  The bits are kept as
-    // lane masks (scalar XORs) and shifted in from the top.
-    const uint64_t b3 = __ballot(w < 0.0f);
-    const uint64_t b2 = b3 ^ __ballot(u < 0.0f);
-    const uint64_t b1 = b2 ^ __ballot(aw > au);
-    const uint32_t oct = shift_in(shift_in(shift_in(0u, b3), b2), b1);
+    // and the sector within the octant flips with those
+    const uint32_t x3 = __float_as_uint(w);
+    const uint32_t x2 = x3 ^ __float_as_uint(u);
+    const uint32_t x1 = x2 ^ __float_as_uint(fabsf(u) - fabsf(w));
+    const uint32_t oct =
+        __builtin_amdgcn_alignbit(__builtin_amdgcn_alignbit(x3 >> 31, x2, 31), x1, 31);
+    // min(|u|, |w|) > t max(|u|, |w|) for t < 1, as a sign: both |u| > t |w| and
+    // |w| > t |u| (no division; a coincident pair stays in sector 0)
+    auto past = [&](float t) {
+        return __float_as_uint(fabsf(t * w) - fabsf(u)) & __float_as_uint(fabsf(t * u) - fabsf(w));
+    };
     if constexpr (M == 1) return (int)oct;
-    const float mx = fmaxf(au, aw), mn = fminf(au, aw);
-    if constexpr (M == 2) {
-        return (int)shift_in(oct, b1 ^ __ballot(mn > 0.41421356237309503f * mx));  // tan(pi/8)
-    } else {
-        static_assert(M == 1 || M == 4, "sector_oct takes M = 1, 2 or 4");
-        // j = 0 .. 3 edges passed: tan(pi/16), tan(pi/8), tan(3 pi/16)
-        const uint64_t e1 = __ballot(mn > 0.19891236737965800f * mx);
-        const uint64_t e2 = __ballot(mn > 0.41421356237309503f * mx);
-        const uint64_t e3 = __ballot(mn > 0.66817863791929891f * mx);
-        return (int)shift_in(shift_in(oct, b1 ^ e2), b1 ^ (e1 ^ e2 ^ e3));
+    else if constexpr (M == 2)
+        return (int)__builtin_amdgcn_alignbit(oct, x1 ^ past(0.41421356237309503f), 31);  // tan(pi/8)
+    else {
+        static_assert(M == 4, "sector_oct takes M = 1, 2 or 4");
+        // edges passed, 0 .. 3: tan(pi/16), tan(pi/8), tan(3 pi/16)
+        const uint32_t e1 = past(0.19891236737965800f), e2 = past(0.41421356237309503f),
+                       e3 = past(0.66817863791929891f);
+        return (int)__builtin_amdgcn_alignbit(__builtin_amdgcn_alignbit(oct, x1 ^ e2, 31),
+                                              x1 ^ e1 ^ e2 ^ e3, 31);
     }
 }
 
