@@ -1544,6 +1544,26 @@ __host__ __device__ constexpr SweepPolLds sweep_pol_lds(int min_words, int A, in
     return SweepPolLds{pc, speed, env, id, hid, hid + (alias ? 0 : (NT / 64) * 16 * kHidLd / 2)};
 }
 
+// Blocks go to the XCDs round robin, and each XCD has an L2 of its own.  The
+// sweep hands each XCD runs of 2^kSweepRun agents' worth of consecutive
+// blocks, so that the agent-order rows and rewards an env's agents write merge
+// into whole lines in one L2, and candidates are read into one, instead of
+// into all eight.  Of the blocks left over after the whole rounds, each XCD
+// takes one eighth, and the last few stay in place.
+// 200 x 5,000 agents: 72.1 -> 68.2 us per step; 20 x 50,000 clustered, four
+// lanes: 257 -> 252.
+constexpr int kSweepRun = 12;
+
+__device__ __forceinline__ int sweep_block(int b, int nb, int log_run) {
+    const int round = nb >> (log_run + 3) << (log_run + 3);
+    if (b < round) {
+        const int k = b >> 3;
+        return ((((k >> log_run) << 3) + (b & 7)) << log_run) + (k & ((1 << log_run) - 1));
+    }
+    const int per = (nb - round) >> 3, r = b - round;
+    return r < per << 3 ? round + (r & 7) * per + (r >> 3) : b;
+}
+
 // 32-bit words of LDS of a sweep block before the policy's: the minima, then
 // (lane groups) each wave's queue.
 __host__ __device__ constexpr int sweep_words(int vs, int NT, int G, int kM) {
@@ -1563,7 +1583,8 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
     __shared__ int s_env;
     __shared__ float *s_orow[G == 1 && kPol == 0 ? NT : 1];  // view rows (one lane per agent)
     const int tid = threadIdx.x, slot = tid / G, li = tid % G;
-    const int p0 = blockIdx.x * A;
+    constexpr int kLogRun = kSweepRun - __builtin_ctz(A);
+    const int p0 = sweep_block((int)blockIdx.x, (int)gridDim.x, kLogRun) * A;
     if constexpr (G == 1) block_env(&s_env, a.base, n_envs, p0);
     uint32_t *smin = s_min + slot;
     if constexpr (G > 1)
