@@ -1545,14 +1545,19 @@ __host__ __device__ constexpr SweepPolLds sweep_pol_lds(int min_words, int A, in
 }
 
 // Blocks go to the XCDs round robin, and each XCD has an L2 of its own.  The
-// sweep hands each XCD runs of 2^kSweepRun agents' worth of consecutive
-// blocks, so that the agent-order rows and rewards an env's agents write merge
-// into whole lines in one L2, and candidates are read into one, instead of
-// into all eight.  Of the blocks left over after the whole rounds, each XCD
-// takes one eighth, and the last few stay in place.
-// 200 x 5,000 agents: 72.1 -> 68.2 us per step; 20 x 50,000 clustered, four
-// lanes: 257 -> 252.
-constexpr int kSweepRun = 12;
+// sweep hands each XCD runs of 2^log_run consecutive blocks, so that the
+// agent-order rows and rewards an env's agents write merge into whole lines in
+// one L2, and candidates are read into one, instead of into all eight.  Of the
+// blocks left over after the whole rounds, each XCD takes one eighth, and the
+// last few stay in place.  With one lane per agent, whose sweep is half bound
+// by those lines, runs hold 8,192 agents (200 x 5,000 agents: 72.1 us per step
+// without runs, 71.3 with 1,024 agents each, 69.5 with 2,048, 68.9 with 4,096,
+// 69.2 with 8,192; 256 uneven envs 82.0, 82.0, 81.0, 79.6, 78.7).  Lane groups
+// sweep dense neighbourhoods, whose agents differ in cost and lie together in
+// cell order: 256 agents keep the XCDs' shares even (20 x 50,000 clustered,
+// four lanes: 257 -> 252 us; 16,000 agents drawn together by their policy, 64
+// lanes: 4.7 ms per 128 steps, 5.1 with runs of 1,024, 5.3 of 4,096).
+constexpr int kSweepRunOne = 13, kSweepRunGroup = 8;  // log2 agents
 
 __device__ __forceinline__ int sweep_block(int b, int nb, int log_run) {
     const int round = nb >> (log_run + 3) << (log_run + 3);
@@ -1583,7 +1588,7 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
     __shared__ int s_env;
     __shared__ float *s_orow[G == 1 && kPol == 0 ? NT : 1];  // view rows (one lane per agent)
     const int tid = threadIdx.x, slot = tid / G, li = tid % G;
-    constexpr int kLogRun = kSweepRun - __builtin_ctz(A);
+    constexpr int kLogRun = (G == 1 ? kSweepRunOne : kSweepRunGroup) - __builtin_ctz(A);
     const int p0 = sweep_block((int)blockIdx.x, (int)gridDim.x, kLogRun) * A;
     if constexpr (G == 1) block_env(&s_env, a.base, n_envs, p0);
     uint32_t *smin = s_min + slot;
