@@ -1066,9 +1066,7 @@ static int rollout_impl(env_batch_t *b, pol_t *pol, pol_t *chaser, int steps, co
             const float *e_k = eps ? eps + (size_t)k * G * 2 : nullptr;
             float *l_k = logp ? logp + (size_t)k * G : nullptr;
             if (tag) {
-                le = policy_launch_typed(pol, b->plan, tk, 0, o_k, e_k, ls, a_k, l_k, s);
-                if (le == hipSuccess)
-                    le = policy_launch_typed(chaser, b->plan, tk, 1, o_k, e_k, ls + 2, a_k, l_k, s);
+                le = policy_launch_types(pol, chaser, b->plan, tk, o_k, e_k, ls, a_k, l_k, s);
             } else if (k == 0 || !fuse_plan) {
                 // the first action; when the plan fuses, each step's view
                 // sweep then computes the next
@@ -1126,9 +1124,8 @@ int env_step_policy_tag(env_batch_t *b, pol_t *runner, pol_t *chaser, float *act
     int t;
     int rc = batch_prepare(b, s, &t);
     if (rc != ENV_OK) return rc;
-    hipError_t e = policy_launch_typed(runner, b->plan, t, 0, obs, nullptr, nullptr, act, nullptr, s);
-    if (e == hipSuccess)
-        e = policy_launch_typed(chaser, b->plan, t, 1, obs, nullptr, nullptr, act, nullptr, s);
+    hipError_t e =
+        policy_launch_types(runner, chaser, b->plan, t, obs, nullptr, nullptr, act, nullptr, s);
     b->plan.strip_now = batch_sorted(b);
     if (e == hipSuccess) e = launch_step(b->plan, t, 1, act, obs, reward, 1, s);
     if (e != hipSuccess) return hip_fail(e, "env_step_policy_tag");

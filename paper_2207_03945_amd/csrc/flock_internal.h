@@ -128,6 +128,25 @@ struct StepPlan {
     int strip_wait = kStripWait;
 };
 
+// Last env e with base[e] <= row (skipping empty envs, whose base equals the
+// next), by the 64 lanes of one wave: each round splits [lo, hi)
+// into 64 strides and keeps the last stride whose first base is <= row
+// (base[lo] <= row holds throughout), so up to 64^k envs take k dependent
+// loads instead of log2 of them.  Every lane of the wave must call it.
+__device__ inline int wave_env_search(const int32_t *base, int n_envs, int row) {
+    const int lane = threadIdx.x & 63;
+    int lo = 0, hi = n_envs;
+    while (hi - lo > 1) {
+        const int step = (hi - lo + 63) >> 6;
+        const int e = lo + lane * step;
+        const bool ok = e < hi && base[e] <= row;
+        const uint64_t m = __ballot(ok);  // lane 0 (e = lo) is always set
+        lo += (63 - __builtin_clzll(m)) * step;
+        hi = hi < lo + step ? hi : lo + step;
+    }
+    return lo;
+}
+
 // Workspace carving --------------------------------------------------------
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -262,10 +281,11 @@ const void *policy_weights(const pol_t *pol);
 // act = mean + exp(log_std) * eps (eps [n][2]), logp [n] (may be null).
 hipError_t policy_launch_sample(const pol_t *pol, const float *obs, int64_t n, const float *eps,
                                 const float log_std[2], float *act, float *logp, hipStream_t s);
-// Tag: rows of one type (1 chasers, 0 runners) of a batch plan; mean
-// action when eps is null, else sampled as policy_launch_sample.
-hipError_t policy_launch_typed(const pol_t *pol, const StepPlan &plan, int table, int type,
-                               const float *obs, const float *eps, const float *log_std,
+// Tag: every row of a batch plan by its type's policy, in one launch; mean
+// actions when eps is null, else sampled as policy_launch_sample (log_std: the
+// runner's two values, then the chaser's).
+hipError_t policy_launch_types(const pol_t *runner, const pol_t *chaser, const StepPlan &plan,
+                               int table, const float *obs, const float *eps, const float *log_std,
                                float *act, float *logp, hipStream_t s);
 // value [n] = critic(obs).
 hipError_t policy_launch_value(const pol_t *pol, const float *obs, int64_t n, float *value,

@@ -72,24 +72,6 @@ __device__ __forceinline__ int env_search(const int32_t *base, int n_envs, int r
     return lo;
 }
 
-// The same search by the 64 lanes of one wave: each round splits [lo, hi)
-// into 64 strides and keeps the last stride whose first base is <= row
-// (base[lo] <= row holds throughout), so up to 64^k envs take k dependent
-// loads instead of log2 of them.  Every lane of the wave must call it.
-__device__ __forceinline__ int wave_env_search(const int32_t *base, int n_envs, int row) {
-    const int lane = threadIdx.x & 63;
-    int lo = 0, hi = n_envs;
-    while (hi - lo > 1) {
-        const int step = (hi - lo + 63) >> 6;
-        const int e = lo + lane * step;
-        const bool ok = e < hi && base[e] <= row;
-        const uint64_t m = __ballot(ok);  // lane 0 (e = lo) is always set
-        lo += (63 - __builtin_clzll(m)) * step;
-        hi = hi < lo + step ? hi : lo + step;
-    }
-    return lo;
-}
-
 constexpr bool kWaveSearch = true;
 
 // Env of the block's first row into s_env (wave 0 searches).

@@ -17,6 +17,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -27,7 +28,6 @@ namespace flock {
 
 namespace {
 
-constexpr int kPolBlock = 256;
 constexpr int kMaxIn = 257;                    // 256 sectors + speed
 
 // kc: chunks of 32 inputs.
@@ -44,17 +44,6 @@ PolLayout carve_pol(char *base, int kc) {
     return l;
 }
 
-// Last env e with base[e] <= row.
-__device__ __forceinline__ int env_of_row(const int32_t *base, int n_envs, int64_t row) {
-    int lo = 0, hi = n_envs - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (base[mid] <= row) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 // What the output layer produces.
 enum PolOut {
     kMean = 0,    // actor: the mean action, tanh-squashed and scaled
@@ -62,173 +51,169 @@ enum PolOut {
     kValue = 2,   // critic: the linear first output
 };
 
-// Per-launch sampling / value arguments (unused fields are ignored).
-struct OutArgs {
-    const float2 *eps;  // [n] standard-normal draws (kSample)
-    float sig0, sig1;   // exp(log_std) per action dimension
-    float logp_c;       // -(log_std0 + log_std1) - log(2 pi)
-    float *logp;        // [n] log density of the sample (kSample, may be null)
-    float *val;         // [n] critic value (kValue)
-    // Tag type filter: when type_want >= 0 only rows of that type (1 chaser,
-    // 0 runner; found through the batch tables) are computed and written.
-    int type_want;
-    const DevEnv *tenvs;
-    const int32_t *tbase;
-    int tn_envs;
+// One network of a launch and its output scales.
+struct NetArgs {
+    PolLayout P;
+    float max_turn, max_dspeed;
+    float sig0, sig1;  // exp(log_std) per action dimension (kSample)
+    float logp_c;      // -(log_std0 + log_std1) - log(2 pi)
 };
 
-// Tile loads a lane keeps in flight while staging obs rows.
-constexpr int kStageLoads = 8;
+struct PolArgs {
+    NetArgs net[2];     // tag launches: [0] runners', [1] chasers' (blockIdx.y picks)
+    int in_dim, kc;     // kc: chunks of 32 inputs
+    int64_t n;
+    const float *obs;   // [n][in_dim]; null: each row's env-owned rows (envs)
+    float2 *act;        // [n], as obs
+    const float2 *eps;  // [n] standard-normal draws (kSample)
+    float *logp;        // [n] log density of the sample (kSample, may be null)
+    float *val;         // [n] critic value (kValue)
+    // batch tables: rows' envs, for env-owned rows and for tag types
+    const DevEnv *envs;
+    const int32_t *base;
+    int n_envs, typed;
+};
 
-// Rows are agents; obs/act are [n][in_dim] / [n][2] arrays, or, when `envs`
-// is non-null, each row's env-owned rows found through the batch tables.
-// Layer 1's results reach layer 2's B operand (eight consecutive hidden units
-// per lane group) through a per-wave LDS tile [16 agents][72] of BF16.
-// kLdsW1: the layer-1 A operand (more than one chunk of 32 inputs) lives in
-// LDS, loaded once per block; kStage (batch-wide obs rows): each wave copies
-// its tile's 16 consecutive rows, one contiguous block of 16 in_dim floats,
-// into LDS as BF16 (zero beyond in_dim) with coalesced 16-byte loads, and the
-// MFMA operands are read from there; otherwise every lane loads its own row.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
-template <bool kLdsW1, int kOut, bool kStage>
-__global__ __launch_bounds__(kPolBlock) void k_policy(PolLayout P, int in_dim, int kc,
-                                                      float max_turn, float max_dspeed,
-                                                      const float *__restrict__ obs, int64_t n,
-                                                      float2 *__restrict__ act,
-                                                      const DevEnv *__restrict__ envs,
-                                                      const int32_t *__restrict__ base,
-                                                      int n_envs, OutArgs oa) {
+// Rows are agents: one wave per 16-row tile, tiles strided over the grid's
+// waves.  Lane (g, col) takes inputs 32 c + 8 g .. + 7 of the tile's row col
+// straight from its row, in two 16-byte loads (rows of any length, so 4-byte
+// aligned) that each chunk issues before the products of the chunk before it,
+// across tiles; the four lane groups read 128 consecutive bytes of each row.
+// Copying tiles through LDS first took some ten vector instructions per input
+// (1M rows of 16: 62.1 -> 39.7 us; critic over 129 x 16,000 rows of 129 and
+// advantages: 300 -> 260 us, the critic's 241 us reading its views at 4.4 TB/s;
+// a large copy moves 5.2).  Bound: tanh on the vector ALUs for short rows (128
+// per row, whose exp and reciprocal issue at a quarter of the rate of an FMA:
+// about 27 us of issue per 1M rows), reading the rows for long ones.
+// Layer 1's A operand lives in LDS, loaded once per block; kReg: the other
+// layers' in registers, else in LDS too.  Layer 1's results reach layer 2's B
+// operand (eight consecutive hidden units per lane group) through a per-wave
+// LDS tile.
+template <int NT, bool kReg, int kOut>
+__global__ __launch_bounds__(NT) void k_policy(PolArgs A) {
     __shared__ PolConsts s_pc;
     extern __shared__ bf16x8 s_dyn[];
-    const int wid = threadIdx.x / 64;
-    bf16x8 *s_w1 = s_dyn;  // [kc][4 tiles][64 lanes] when kLdsW1
-    __bf16 *s_hid = reinterpret_cast<__bf16 *>(s_dyn + (kLdsW1 ? kc * 256 : 0)) +
-                    (size_t)wid * 16 * kHidLd;
-    // per-wave obs tiles after the hidden tiles: [16 rows][ld] BF16, ld = 32 kc + 8
-    const int ld = 32 * kc + 8;
-    __bf16 *s_obs = reinterpret_cast<__bf16 *>(s_dyn + (kLdsW1 ? kc * 256 : 0)) +
-                    (size_t)(kPolBlock / 64) * 16 * kHidLd + (size_t)wid * 16 * ld;
-    if (kLdsW1)
-        for (int i = threadIdx.x; i < kc * 256; i += kPolBlock) s_w1[i] = P.w1[i];
-    load_pol_consts(P, &s_pc, threadIdx.x, kPolBlock);
+    const int wid = threadIdx.x / 64, lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+    const int type = (int)blockIdx.y;
+    const NetArgs N = type ? A.net[1] : A.net[0];
+    const int kc = A.kc, in_dim = A.in_dim, rem = in_dim & 7;
+    bf16x8 *s_w1 = s_dyn, *s_w2 = s_w1 + kc * 256, *s_w3 = s_w2 + (kReg ? 0 : 512);
+    __bf16 *s_hid = reinterpret_cast<__bf16 *>(s_w3 + (kReg ? 0 : 128)) + (size_t)wid * 16 * kHidLd;
+    const int64_t waves = (int64_t)gridDim.x * (NT / 64);
+    const int64_t tiles = (A.n + 15) / 16;
+
+    // the lane's row of a tile: its env-owned rows, whether it is computed
+    struct Row {
+        const float *x;
+        float2 *act;
+        bool valid;
+    };
+    auto row_of = [&](int64_t tile) {
+        const int64_t agent = tile * 16 + col;
+        const int64_t at = agent < A.n ? agent : A.n - 1;  // rows past the end repeat the last
+        Row r{A.obs + at * in_dim, A.act + at, agent < A.n};
+        if (A.envs) {
+            int e = 0;
+            if (A.n_envs > 1) {
+                e = wave_env_search(A.base, A.n_envs, (int)(tile * 16));
+                while (A.base[e + 1] <= at) ++e;
+            }
+            const DevEnv &E = A.envs[e];
+            const int64_t i = at - E.agent_base;
+            if (A.typed) {
+                r.valid = r.valid && (i < E.n_chasers ? 1 : 0) == type;
+            } else {
+                r.x = E.obs + i * in_dim;
+                r.act = reinterpret_cast<float2 *>(E.act) + i;
+            }
+        }
+        return r;
+    };
+    // the wave's first tile from `tile` on that has a row to compute
+    auto find = [&](int64_t tile, Row &r) {
+        for (; tile < tiles; tile += waves) {
+            r = row_of(tile);
+            if (!A.typed || __any(r.valid)) break;
+        }
+        return tile;
+    };
+    auto load = [&](const Row &r, int c, float (&f)[8]) {
+        const int k0 = 32 * c + 8 * g;
+        if (k0 + 8 <= in_dim) {
+            const f32x4u u = *reinterpret_cast<const f32x4u *>(r.x + k0);
+            const f32x4u w = *reinterpret_cast<const f32x4u *>(r.x + k0 + 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                f[j] = u[j];
+                f[4 + j] = w[j];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = 0.0f;
+            if (k0 < in_dim) {
+#pragma unroll
+                for (int j = 0; j < 7; ++j)
+                    if (j < rem) f[j] = r.x[k0 + j];
+            }
+        }
+    };
+
+    Row row{};
+    float f[8];
+    int64_t tile = find((int64_t)blockIdx.x * (NT / 64) + wid, row);
+    if (tile < tiles) load(row, 0, f);
+    for (int i = threadIdx.x; i < kc * 256; i += NT) s_w1[i] = N.P.w1[i];
+    bf16x8 w2[kReg ? 8 : 1], w3[kReg ? 2 : 1];
+    if constexpr (kReg) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w2[k] = N.P.w2[k * 64 + lane];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) w3[k] = N.P.w3[k * 64 + lane];
+    } else {
+        for (int i = threadIdx.x; i < 512; i += NT) s_w2[i] = N.P.w2[i];
+        if (threadIdx.x < 128) s_w3[threadIdx.x] = N.P.w3[threadIdx.x];
+    }
+    load_pol_consts(N.P, &s_pc, threadIdx.x, NT);
     __syncthreads();
 
-    const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
-    bf16x8 w1[4];
-    if (!kLdsW1)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) w1[t] = P.w1[t * 64 + lane];  // kc == 1
-    bf16x8 w2[2][4], w3[2];
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) w2[c][t] = P.w2[(c * 4 + t) * 64 + lane];
-        w3[c] = P.w3[c * 64 + lane];
-    }
-
-    const int64_t waves = (int64_t)gridDim.x * (kPolBlock / 64);
-    const int64_t tiles = (n + 15) / 16;
-    for (int64_t tile = (int64_t)blockIdx.x * (kPolBlock / 64) + wid; tile < tiles;
-         tile += waves) {
-        const int64_t agent = tile * 16 + col;
-        bool valid = agent < n;
-        if (oa.type_want >= 0) {
-            if (valid) {
-                const DevEnv &T = oa.tenvs[env_of_row(oa.tbase, oa.tn_envs, agent)];
-                valid = ((agent - T.agent_base) < T.n_chasers ? 1 : 0) == oa.type_want;
-            }
-            if (!__any(valid)) continue;  // no row of this type in the tile
-        }
-        const float *orow = obs + agent * in_dim;
-        float2 *arow = act + agent;
-        if constexpr (kStage) {
-            const int64_t row0 = tile * 16;
-            const int rows = n - row0 < 16 ? (int)(n - row0) : 16;
-            const float *src = obs + row0 * in_dim;
-            const int cnt = rows * in_dim, cnt4 = cnt >> 2;
-            wave_lds_fence();  // the previous tile's reads come first
-            // zero the tile (columns past in_dim must read as 0)
-            uint4 *z = reinterpret_cast<uint4 *>(s_obs);
-            for (int i = lane; i < 2 * ld; i += 64) z[i] = make_uint4(0u, 0u, 0u, 0u);
-            wave_lds_fence();
-            int rb = (4 * lane) / in_dim, kb = 4 * lane - rb * in_dim;
-            const int dq = 256 / in_dim, dr = 256 - dq * in_dim;
-            const float4 *src4 = reinterpret_cast<const float4 *>(src);
-            for (int eb = lane; eb < cnt4; eb += 64 * kStageLoads) {
-                float4 q[kStageLoads];
-#pragma unroll
-                for (int u = 0; u < kStageLoads; ++u) {
-                    const int e4 = eb + 64 * u;
-                    q[u] = src4[e4 < cnt4 ? e4 : cnt4 - 1];  // unconditional: all in flight
-                }
-#pragma unroll
-                for (int u = 0; u < kStageLoads; ++u) {
-                    int r = rb, k = kb;
-                    rb += dq;
-                    kb += dr;
-                    if (kb >= in_dim) {
-                        kb -= in_dim;
-                        ++rb;
-                    }
-                    if (eb + 64 * u >= cnt4) continue;
-                    const float qv[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        s_obs[r * ld + k] = (__bf16)qv[v];
-                        if (++k == in_dim) {
-                            k = 0;
-                            ++r;
-                        }
-                    }
-                }
-            }
-            for (int e = 4 * cnt4 + lane; e < cnt; e += 64) {
-                const int r = e / in_dim;
-                s_obs[r * ld + (e - r * in_dim)] = (__bf16)src[e];
-            }
-            wave_lds_fence();  // this wave's copies before its reads
-        }
-        if (envs && valid) {
-            const DevEnv &E = envs[env_of_row(base, n_envs, agent)];
-            const int64_t i = agent - E.agent_base;
-            orow = E.obs + i * in_dim;
-            arow = reinterpret_cast<float2 *>(E.act) + i;
-        }
-        // the tile's eight inputs 32 c + 8 g .. + 7 of agent col, as BF16
+    while (tile < tiles) {
+        Row next{};
+        const int64_t tnext = find(tile + waves, next);
+        // the tile's inputs as BF16, the next chunk's (or tile's) loads issued
         auto xb = [&](int c) {
             bf16x8 x;
-            const int k0 = 32 * c + 8 * g;
-            if constexpr (kStage) {
-                x = *reinterpret_cast<const bf16x8 *>(s_obs + col * ld + k0);
-            } else if (valid && in_dim % 4 == 0 && k0 + 8 <= in_dim) {
-                const float4 *src = reinterpret_cast<const float4 *>(orow + k0);
-                const float4 u = src[0], w = src[1];
-                x[0] = (__bf16)u.x; x[1] = (__bf16)u.y; x[2] = (__bf16)u.z; x[3] = (__bf16)u.w;
-                x[4] = (__bf16)w.x; x[5] = (__bf16)w.y; x[6] = (__bf16)w.z; x[7] = (__bf16)w.w;
-            } else {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int k = k0 + j;
-                    x[j] = (__bf16)((valid && k < in_dim) ? orow[k] : 0.0f);
-                }
-            }
+            for (int j = 0; j < 8; ++j) x[j] = (__bf16)f[j];
+            if (c + 1 < kc) load(row, c + 1, f);
+            else if (tnext < tiles) load(next, 0, f);
             return x;
         };
-        auto w1a = [&](int c, int t) { return kLdsW1 ? s_w1[(c * 4 + t) * 64 + lane] : w1[t]; };
-        auto w2a = [&](int c, int t) { return w2[c][t]; };
-        auto w3a = [&](int c) { return w3[c]; };
+        auto w1a = [&](int c, int t) { return s_w1[(c * 4 + t) * 64 + lane]; };
+        auto w2a = [&](int c, int t) {
+            if constexpr (kReg) return w2[c * 4 + t];
+            else return s_w2[(c * 4 + t) * 64 + lane];
+        };
+        auto w3a = [&](int c) {
+            if constexpr (kReg) return w3[c];
+            else return s_w3[c * 64 + lane];
+        };
         auto hrow = [&](int r) { return s_hid + r * kHidLd; };
         const float2 z = mlp_tile(kc, xb, w1a, w2a, w3a, s_pc, hrow, lane);
-        if (g == 0 && valid) {
+        if (g == 0 && row.valid) {
+            const int64_t agent = tile * 16 + col;
             if constexpr (kOut == kValue) {
-                oa.val[agent] = z.x;
+                A.val[agent] = z.x;
             } else {
-                const float2 e = kOut == kSample ? oa.eps[agent] : make_float2(0.0f, 0.0f);
-                *arow = pol_output<kOut == kSample>(z, max_turn, max_dspeed, e, oa.sig0,
-                                                   oa.sig1, oa.logp_c,
-                                                   oa.logp ? oa.logp + agent : nullptr);
+                const float2 e = kOut == kSample ? A.eps[agent] : make_float2(0.0f, 0.0f);
+                *row.act = pol_output<kOut == kSample>(z, N.max_turn, N.max_dspeed, e, N.sig0,
+                                                       N.sig1, N.logp_c,
+                                                       A.logp ? A.logp + agent : nullptr);
             }
         }
+        tile = tnext;
+        row = next;
     }
 }
 
@@ -264,89 +249,94 @@ struct flock_policy {
 namespace flock {
 
 namespace {
-OutArgs no_filter() {
-    OutArgs oa{};
-    oa.type_want = -1;
-    return oa;
+NetArgs net_args(const pol_t *p, const float *log_std) {
+    NetArgs n{};
+    n.P = p->lay;
+    n.max_turn = p->max_turn;
+    n.max_dspeed = p->max_dspeed;
+    if (log_std) {
+        n.sig0 = (float)exp((double)log_std[0]);
+        n.sig1 = (float)exp((double)log_std[1]);
+        n.logp_c = (float)(-((double)log_std[0] + (double)log_std[1]) - log(2.0 * M_PI));
+    }
+    return n;
+}
+
+PolArgs pol_args(const pol_t *p, const float *log_std, const float *obs, int64_t n, float *act) {
+    PolArgs a{};
+    a.net[0] = net_args(p, log_std);
+    a.in_dim = p->in_dim;
+    a.kc = p->kc;
+    a.n = n;
+    a.obs = obs;
+    a.act = reinterpret_cast<float2 *>(act);
+    return a;
 }
 
 template <int kOut>
-hipError_t launch_pol(const pol_t *p, const float *obs, int64_t n, float *act, const DevEnv *envs,
-                      const int32_t *base, int n_envs, const OutArgs &oa, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const int kc = p->kc;
-    const int64_t tiles = (n + 15) / 16;
-    int64_t blocks = (tiles + 3) / 4;
-    if (blocks > 4096) blocks = 4096;
-    float2 *a2 = reinterpret_cast<float2 *>(act);
-    const bool lds_w1 = kc > 1;
-    const size_t w1b = lds_w1 ? (size_t)kc * 256 * sizeof(bf16x8) : 0;
-    const size_t hid_b = (size_t)(kPolBlock / 64) * 16 * kHidLd * sizeof(__bf16);
-    const size_t tile_b = (size_t)(kPolBlock / 64) * 16 * (32 * kc + 8) * sizeof(__bf16);
-    // batch-wide rows whose tiles start 16-byte aligned are staged through LDS
-    // (within the 64 KiB of dynamic LDS a launch gets by default)
-    const bool stage = obs && !envs && (reinterpret_cast<uintptr_t>(obs) & 15) == 0 &&
-                       w1b + hid_b + tile_b <= 65536;
-    const size_t lds = w1b + hid_b + (stage ? tile_b : 0);
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kPolBlock), lds, s, p->lay,
-                           p->in_dim, kc, p->max_turn, p->max_dspeed, obs, n, a2, envs, base,
-                           n_envs, oa);
+hipError_t launch_pol(const PolArgs &a, hipStream_t s) {
+    if (a.n <= 0) return hipSuccess;
+    const int64_t tiles = (a.n + 15) / 16;
+    auto go = [&](auto kernel, int nt, bool reg, int64_t most) {
+        const int64_t blocks = std::min<int64_t>((tiles + nt / 64 - 1) / (nt / 64), most);
+        const size_t lds = ((size_t)a.kc * 256 + (reg ? 0 : 640)) * sizeof(bf16x8) +
+                           (size_t)(nt / 64) * 16 * kHidLd * sizeof(__bf16);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks, a.typed ? 2 : 1), dim3(nt), lds, s, a);
     };
-    if (lds_w1) {
-        if (stage) go(k_policy<true, kOut, true>);
-        else go(k_policy<true, kOut, false>);
-    } else {
-        if (stage) go(k_policy<false, kOut, true>);
-        else go(k_policy<false, kOut, false>);
-    }
+    // Short rows (one chunk) of large launches: the weights in LDS leave 70
+    // registers, seven waves a SIMD (1M rows: 39.7 us; with the weights in 56
+    // registers, four waves, 49.3; two tiles side by side to a wave, 53), in
+    // more blocks than are resident, so that the last round is even (1,024
+    // blocks 44.2 us, 1,536 41.3, 2,048 39.7, 4,096 40.1).  Long rows are
+    // bound by their reads, and the LDS by layer 1's operands (four waves and
+    // registers 261 us, all in LDS 309); small launches by one tile's latency.
+    if (a.kc == 1 && tiles > 4096) go(k_policy<512, false, kOut>, 512, false, 2048);
+    else go(k_policy<256, true, kOut>, 256, true, 1024);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t policy_launch(const pol_t *p, const float *obs, int64_t n, float *act, hipStream_t s) {
-    return launch_pol<kMean>(p, obs, n, act, nullptr, nullptr, 0, no_filter(), s);
+    return launch_pol<kMean>(pol_args(p, nullptr, obs, n, act), s);
 }
 
 hipError_t policy_launch_sample(const pol_t *p, const float *obs, int64_t n, const float *eps,
                                 const float log_std[2], float *act, float *logp, hipStream_t s) {
-    OutArgs oa = no_filter();
-    oa.eps = reinterpret_cast<const float2 *>(eps);
-    oa.sig0 = (float)exp((double)log_std[0]);
-    oa.sig1 = (float)exp((double)log_std[1]);
-    oa.logp_c = (float)(-((double)log_std[0] + (double)log_std[1]) - log(2.0 * M_PI));
-    oa.logp = logp;
-    return launch_pol<kSample>(p, obs, n, act, nullptr, nullptr, 0, oa, s);
+    PolArgs a = pol_args(p, log_std, obs, n, act);
+    a.eps = reinterpret_cast<const float2 *>(eps);
+    a.logp = logp;
+    return launch_pol<kSample>(a, s);
 }
 
 hipError_t policy_launch_value(const pol_t *p, const float *obs, int64_t n, float *val,
                                hipStream_t s) {
-    OutArgs oa = no_filter();
-    oa.val = val;
-    return launch_pol<kValue>(p, obs, n, nullptr, nullptr, nullptr, 0, oa, s);
+    PolArgs a = pol_args(p, nullptr, obs, n, nullptr);
+    a.val = val;
+    return launch_pol<kValue>(a, s);
 }
 
-hipError_t policy_launch_typed(const pol_t *p, const StepPlan &plan, int table, int type,
-                               const float *obs, const float *eps, const float *log_std,
+hipError_t policy_launch_types(const pol_t *runner, const pol_t *chaser, const StepPlan &plan,
+                               int table, const float *obs, const float *eps, const float *log_std,
                                float *act, float *logp, hipStream_t s) {
-    OutArgs oa{};
-    oa.type_want = type;
-    oa.tenvs = plan.a.envs[table & 1];
-    oa.tbase = plan.a.base;
-    oa.tn_envs = plan.n_envs;
-    if (!eps) return launch_pol<kMean>(p, obs, plan.G, act, nullptr, nullptr, 0, oa, s);
-    oa.eps = reinterpret_cast<const float2 *>(eps);
-    oa.sig0 = (float)exp((double)log_std[0]);
-    oa.sig1 = (float)exp((double)log_std[1]);
-    oa.logp_c = (float)(-((double)log_std[0] + (double)log_std[1]) - log(2.0 * M_PI));
-    oa.logp = logp;
-    return launch_pol<kSample>(p, obs, plan.G, act, nullptr, nullptr, 0, oa, s);
+    PolArgs a = pol_args(runner, log_std, obs, plan.G, act);
+    a.net[1] = net_args(chaser, log_std ? log_std + 2 : nullptr);
+    a.typed = 1;
+    a.envs = plan.a.envs[table & 1];
+    a.base = plan.a.base;
+    a.n_envs = plan.n_envs;
+    if (!eps) return launch_pol<kMean>(a, s);
+    a.eps = reinterpret_cast<const float2 *>(eps);
+    a.logp = logp;
+    return launch_pol<kSample>(a, s);
 }
 
 hipError_t policy_launch_envs(const pol_t *p, const StepPlan &plan, int table, hipStream_t s) {
-    return launch_pol<kMean>(p, nullptr, plan.G, nullptr, plan.a.envs[table & 1], plan.a.base,
-                             plan.n_envs, no_filter(), s);
+    PolArgs a = pol_args(p, nullptr, nullptr, plan.G, nullptr);
+    a.envs = plan.a.envs[table & 1];
+    a.base = plan.a.base;
+    a.n_envs = plan.n_envs;
+    return launch_pol<kMean>(a, s);
 }
 
 int policy_is_critic(const pol_t *p) { return p->critic; }
