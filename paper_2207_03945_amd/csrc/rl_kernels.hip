@@ -9,10 +9,12 @@
 //     A_T = 0,   R_t = A_t + V_t.
 // One thread per agent walks t backwards; rows t of the [T][n] buffers are
 // contiguous over agents, so every load and store is coalesced.  The
-// recurrence runs in FP64 and each output is rounded once to FP32.  Loads
-// for kChunk steps are issued before the chunk's recurrence, so a wave keeps
-// kChunk rows of both inputs in flight (the kernel is HBM-bound: 16 bytes per
-// agent-step).
+// recurrence runs in FP64 and each output is rounded once to FP32.  Bound: HBM
+// (16 bytes per agent-step) for many agents, the latency of T / kChunk rounds
+// of loads for few.  So the next chunk's loads are issued before a chunk's
+// recurrence, and blocks are single waves, one agent a lane, to spread over
+// the CUs (16,000 agents, 128 steps: 250 blocks on 256 CUs instead of 63; the
+// critic and the advantages together 261 -> 254 us).
 #include <math.h>
 
 #include "flock_internal.h"
@@ -21,7 +23,7 @@ namespace flock {
 
 namespace {
 
-constexpr int kGaeBlock = 256;
+constexpr int kGaeBlock = 64;
 constexpr int kChunk = 16;
 
 __global__ __launch_bounds__(kGaeBlock) void k_gae(int T, int64_t n, double gamma, double gl,
@@ -31,34 +33,42 @@ __global__ __launch_bounds__(kGaeBlock) void k_gae(int T, int64_t n, double gamm
                                                    float *__restrict__ ret) {
     const int64_t i = (int64_t)blockIdx.x * kGaeBlock + threadIdx.x;
     if (i >= n) return;
-    double a = 0.0;
-    double v_next = (double)val[(size_t)T * n + i];
-    int t1 = T;  // steps [t1 - kChunk, t1) are next
-    for (; t1 >= kChunk; t1 -= kChunk) {
-        float r[kChunk], v[kChunk];
+    double a = 0.0, v_next = (double)val[(size_t)T * n + i];
+    auto step = [&](size_t at, float r, float v) {
+        const double vt = (double)v;
+        a = ((double)r + gamma * v_next - vt) + gl * a;
+        adv[at] = (float)a;
+        ret[at] = (float)(a + vt);
+        v_next = vt;
+    };
+    // steps t1 - 1 .. t1 - kChunk of both inputs
+    auto load = [&](int t1, float (&r)[kChunk], float (&v)[kChunk]) {
 #pragma unroll
         for (int u = 0; u < kChunk; ++u) {
             const size_t at = (size_t)(t1 - 1 - u) * n + i;
             r[u] = rew[at];
             v[u] = val[at];
         }
+    };
+    auto run = [&](int t1, const float (&r)[kChunk], const float (&v)[kChunk]) {
 #pragma unroll
-        for (int u = 0; u < kChunk; ++u) {
-            const size_t at = (size_t)(t1 - 1 - u) * n + i;
-            const double vt = (double)v[u];
-            a = ((double)r[u] + gamma * v_next - vt) + gl * a;
-            adv[at] = (float)a;
-            ret[at] = (float)(a + vt);
-            v_next = vt;
-        }
+        for (int u = 0; u < kChunk; ++u) step((size_t)(t1 - 1 - u) * n + i, r[u], v[u]);
+    };
+    float r0[kChunk], v0[kChunk], r1[kChunk], v1[kChunk];
+    int t1 = T;  // steps below t1 are left; a whole chunk of them is in (r0, v0)
+    if (t1 >= kChunk) load(t1, r0, v0);
+    while (t1 >= kChunk) {
+        if (t1 >= 2 * kChunk) load(t1 - kChunk, r1, v1);
+        run(t1, r0, v0);
+        t1 -= kChunk;
+        if (t1 < kChunk) break;
+        if (t1 >= 2 * kChunk) load(t1 - kChunk, r0, v0);
+        run(t1, r1, v1);
+        t1 -= kChunk;
     }
     for (int t = t1 - 1; t >= 0; --t) {
         const size_t at = (size_t)t * n + i;
-        const double vt = (double)val[at];
-        a = ((double)rew[at] + gamma * v_next - vt) + gl * a;
-        adv[at] = (float)a;
-        ret[at] = (float)(a + vt);
-        v_next = vt;
+        step(at, rew[at], val[at]);
     }
 }
 
