@@ -405,9 +405,10 @@ int env_step_policy(env_batch_t *b, pol_t *pol, float *act, float *obs, float *r
  *   weight   device FP32 [n_edges]
  *   op_in, op_out  device FP32 [n], distinct
  * Updates run in FP64, rounded once to FP32.  lanes: lanes per node (1, 4,
- * 16, 64; 0 = from the mean degree).  With lanes = 1 each node applies its
- * edges one by one in the stated order; with more, chunks of the row are
- * composed as affine maps (the same map up to FP64 rounding).  0 <= n <
+ * 16, 64; 0 = from the mean degree and the number of edges, where short rows
+ * may be taken in blocks).  With lanes = 1 each node applies its edges one by
+ * one in the stated order; otherwise parts of the row may be composed as
+ * affine maps (the same map up to FP64 rounding).  0 <= n <
  * 2^31.  ENV_EINVAL on bad sizes, NULL arrays, op_in == op_out. */
 int gr_opinion_step(int64_t n, int64_t n_edges, const int64_t *row_ptr, const int32_t *col,
                     const float *weight, float threshold, float strength, const float *op_in,

@@ -145,12 +145,146 @@ void launch_opinion(int64_t n, int64_t n_edges, const int64_t *row_ptr, const in
                        row_ptr, col, weight, thr, strength, op_in, op_out);
 }
 
-// Lanes per node from the mean degree.  Power-law rows are uneven, so wide
-// groups pay off early: on MI355X a 1M-node graph of mean degree 14 steps in
-// 0.21 / 0.139 / 0.338 ms with 4 / 16 / 64 lanes.
+// The tile kernel, for many short rows.  With lanes sharing a node, a row of 14
+// edges gives 16 lanes one edge each in slots for kEdgeBatch of them, so most
+// loads and FP64 maps are padding, and a row of thousands of edges is a long
+// chain of loads in its few lanes.  Here a block takes kTileNodes consecutive
+// nodes, whose edges are one range, and brings it into LDS tile by tile with
+// all its threads: consecutive loads, kTileLoads targets and then as many
+// opinions in flight per thread, the opinion and the weight of an edge kept as a
+// pair.  Then each lane applies its node's edges one by one in the stated order;
+// a node with kTileRow or more edges in the tile is applied by its wave, lane l
+// composing the l-th part of them, the parts composed in order.  What is left
+// is the scattered read of the opinions: 64 lanes ask for 64 lines, about
+// 15 M requests of the L2 per step of the first graph below, 5 in 6 of which hit.
+//
+// MI355X, per step, power-law rows (longest 2000), lanes per node / tiles:
+// 1M nodes of mean degree 14, 139 / 103 us; of 8, 115 / 69; of 5.4, 137 / 53.
+// 128 nodes and 1024 edges: 256 and 2048 take 104, 512 and 4096 123, 64 and 768
+// 110, 128 and 2304 106.  4 loads: 106.  kTileRow 24 or 32 gives up the order at
+// rows where one lane is as fast, and then takes 45 us for 10,000 rows of 30
+// edges that 64 does in 16.
+constexpr int kTileNodes = 128, kTileEdges = 1024, kTileRow = 64, kTileLoads = 8;
+
+__global__ __launch_bounds__(kTileNodes) void k_opinion_tile(int64_t n, int64_t n_edges,
+                                                          const int64_t *__restrict__ row_ptr,
+                                                          const int32_t *__restrict__ col,
+                                                          const float *__restrict__ weight,
+                                                          float thr, double strength,
+                                                          const float *__restrict__ op_in,
+                                                          float *__restrict__ op_out) {
+    __shared__ float2 s_edge[kTileEdges];  // (opinion, weight); NaN opinion: no such node
+    __shared__ int64_t s_lo, s_hi;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t first = (int64_t)blockIdx.x * kTileNodes, i = first + tid;
+    const bool active = i < n;
+    const int64_t r0 = active ? row_ptr[i] : 0, r1 = active ? row_ptr[i + 1] : 0;
+    const float me = active ? op_in[i] : 0.0f;
+    double x = (double)me;
+    // rows that ascend within [0, n_edges] lie end to end
+    const bool csr = !active || (r0 >= 0 && r0 <= r1 && r1 <= n_edges);
+    if (tid == 0) s_lo = r0;
+    if (active && (tid == kTileNodes - 1 || i == n - 1)) s_hi = r1;
+    if (!__syncthreads_and(csr ? 1 : 0)) {
+        // anything else: the clamped ranges, node by node from memory
+        if (!active) return;
+        const int64_t e0 = r0 < 0 ? 0 : (r0 > n_edges ? n_edges : r0);
+        const int64_t e1 = r1 < e0 ? e0 : (r1 > n_edges ? n_edges : r1);
+        for (int64_t e = e0; e < e1; ++e) {
+            const int32_t j = col[e];
+            if (j < 0 || (int64_t)j >= n) continue;
+            const float you = op_in[j];
+            if (fabsf(me - you) < thr) {
+                const double w = strength * (double)weight[e];
+                x = (1.0 - w) * x + w * (double)you;
+            }
+        }
+        op_out[i] = (float)x;
+        return;
+    }
+    const int64_t lo = s_lo, hi = s_hi;
+    for (int64_t t0 = lo; t0 < hi; t0 += kTileEdges) {
+        const int len = hi - t0 < kTileEdges ? (int)(hi - t0) : kTileEdges;
+        for (int k0 = tid; k0 < len; k0 += kTileNodes * kTileLoads) {
+            int32_t j[kTileLoads];
+            float wt[kTileLoads], you[kTileLoads];
+#pragma unroll
+            for (int u = 0; u < kTileLoads; ++u) {
+                const int k = k0 + u * kTileNodes;
+                const int64_t e = t0 + (k < len ? k : k0);
+                j[u] = col[e];
+                wt[u] = weight[e];
+            }
+#pragma unroll
+            for (int u = 0; u < kTileLoads; ++u) {
+                const bool ok = j[u] >= 0 && (int64_t)j[u] < n;
+                const float y = op_in[ok ? j[u] : 0];
+                you[u] = ok ? y : __builtin_nanf("");
+            }
+#pragma unroll
+            for (int u = 0; u < kTileLoads; ++u) {
+                const int k = k0 + u * kTileNodes;
+                if (k < len) s_edge[k] = make_float2(you[u], wt[u]);
+            }
+        }
+        __syncthreads();
+        // the node's edges in the tile
+        const int64_t f0 = r0 > t0 ? r0 - t0 : 0, f1 = r1 - t0 < len ? r1 - t0 : len;
+        const int b0 = (int)f0, b1 = f1 > f0 ? (int)f1 : (int)f0;
+        const bool big = b1 - b0 >= kTileRow;
+        for (int b = b0; b < (big ? b0 : b1); ++b) {
+            const float2 ed = s_edge[b];
+            if (fabsf(me - ed.x) < thr) {
+                const double w = strength * (double)ed.y;
+                x = (1.0 - w) * x + w * (double)ed.x;
+            }
+        }
+        for (uint64_t todo = __ballot(big); todo != 0; todo &= todo - 1) {
+            const int o = __builtin_ctzll(todo);
+            const int q0 = __builtin_amdgcn_readlane(b0, o), q1 = __builtin_amdgcn_readlane(b1, o);
+            const float own = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(me), o));
+            const int part = (q1 - q0 + 63) >> 6;
+            const int c0 = min(q0 + lane * part, q1), c1 = min(c0 + part, q1);
+            double a = 1.0, s = 0.0;  // x -> a x + s over this lane's part
+            for (int b = c0; b < c1; ++b) {
+                const float2 ed = s_edge[b];
+                if (fabsf(own - ed.x) < thr) {
+                    const double w = strength * (double)ed.y;
+                    a = (1.0 - w) * a;
+                    s = (1.0 - w) * s + w * (double)ed.x;
+                }
+            }
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {  // later parts applied last
+                const double pa = __shfl_xor(a, off, 64), ps = __shfl_xor(s, off, 64);
+                s = (lane & off) ? a * ps + s : pa * s + ps;
+                a = a * pa;
+            }
+            if (lane == o) x = a * x + s;
+        }
+        __syncthreads();
+    }
+    if (active) op_out[i] = (float)x;
+}
+
+// Tiles or lanes per node, where the caller leaves the choice.  Below 3 edges a
+// node, one lane per node reads little that it does not need (1M rows of 1 to 3:
+// 17 us, tiles 20).  From 3 to 8, tiles: power-law rows take 8 to 14 us at 3,000 to
+// 30,000 nodes where 4 lanes take 14 to 60 (the longest row's chain), even rows the
+// same up to 30,000 nodes and at 1M, 5 to 10 % more at 100,000 to 300,000.
+// From 8 to 24, tiles once there are edges enough to keep every CU at work through
+// both phases of a tile: 200,000 nodes of mean degree 14 (2.8 M edges) take 37 us
+// with 16 lanes and 34 with tiles, 100,000 take 24 and 32, 300,000 even rows
+// of 8 (2.4 M) 15.5 and 15.9.  Above, a lane's share of a row fills its slots:
+// 300,000 rows of 30 take 50 us with 16 lanes and 53 with tiles, of 48, 72 and 130.
+bool graph_use_tiles(int64_t n_edges, double mean_degree) {
+    return mean_degree >= 3.0 && (mean_degree < 8.0 || (mean_degree < 24.0 && n_edges >= 2500000));
+}
+
+// Lanes per node for the rest, from the mean degree: power-law rows are uneven,
+// so wide groups pay off early.
 int graph_auto_lanes(double mean_degree) {
     if (mean_degree < 3.0) return 1;
-    if (mean_degree < 8.0) return 4;
     if (mean_degree < 256.0) return 16;
     return 64;
 }
@@ -176,9 +310,18 @@ int gr_opinion_step(int64_t n, int64_t n_edges, const int64_t *row_ptr, const in
     if (!row_ptr || !op_in || !op_out || (n_edges > 0 && (!col || !weight)))
         return set_error(ENV_EINVAL, "NULL array");
     if (op_in == op_out) return set_error(ENV_EINVAL, "op_in and op_out must differ");
-    const int g = lanes ? lanes : graph_auto_lanes((double)n_edges / (double)n);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const double st = (double)strength;
+    const double mean = (double)n_edges / (double)n;
+    if (lanes == 0 && graph_use_tiles(n_edges, mean)) {
+        hipLaunchKernelGGL(k_opinion_tile, dim3((unsigned)((n + kTileNodes - 1) / kTileNodes)),
+                           dim3(kTileNodes), 0, s, n, n_edges, row_ptr, col, weight, threshold, st,
+                           op_in, op_out);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return set_error(ENV_EHIP, "gr_opinion_step: %s", hipGetErrorString(e));
+        return ENV_OK;
+    }
+    const int g = lanes ? lanes : graph_auto_lanes(mean);
     auto run = [&](auto tag) {
         constexpr int G = decltype(tag)::value;
         launch_opinion<G>(n, n_edges, row_ptr, col, weight, threshold, st, op_in, op_out, s);

@@ -1,0 +1,88 @@
+"""GPU graph interaction where the lanes per node are left to the library and it
+takes tiles of edges (mean degree 3 to 8, or up to 24 with 2.5 M edges).
+
+A node whose edges in a tile number less than 64 applies them one by one in FP64,
+so its FP32 output is bitwise the oracle's rounded result; longer rows compose
+parts of the row, the same map up to FP64 rounding, so they are within one FP32
+ulp (a compose of at most 64 parts errs by some 1e-14, far below the 6e-8 of the
+last rounding, which it can move by one place only).
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import graph
+
+pytestmark = pytest.mark.gpu
+flock = pytest.importorskip("paper_2207_03945_amd")
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def step(rp, col, w, op):
+    out = torch.empty(op.shape[0], device="cuda")
+    flock.opinion_step(dev(rp), dev(col), dev(w), dev(op), out, 0.4, 0.5)
+    return out.cpu().numpy()
+
+
+def check(got, want, rows_len):
+    want = want.astype(np.float32)
+    off = np.abs(got.view(np.int32).astype(np.int64) - want.view(np.int32).astype(np.int64))
+    assert not off[rows_len < 64].any() and (off <= 1).all()
+
+
+def make(lens, seed, n=None):
+    g = np.random.default_rng(seed)
+    n = len(lens) if n is None else n
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    e = int(rp[-1])
+    return (rp, g.integers(0, n, e).astype(np.int32), g.random(e).astype(np.float32),
+            g.random(n).astype(np.float32))
+
+
+@pytest.mark.parametrize("n,long", [(1, ()), (127, ()), (128, (63, 64, 65)), (129, ()),
+                                    (1000, (63, 64, 65, 1023)), (1500, (1024, 1025)),
+                                    (1900, (3000,))])
+def test_tile_edges(n, long):
+    """Blocks' and tiles' edges: node counts round the block, rows round the length
+    that the wave takes over and round a whole tile, rows across tiles, empty rows."""
+    g = np.random.default_rng(n)
+    lens = g.integers(0, 9, n) if n > 1 else np.array([5])
+    for k, length in enumerate(long):
+        lens[(17 + 31 * k) % n] = length
+    assert 3.0 <= lens.sum() / n < 8.0
+    rp, col, w, op = make(lens, seed=n)
+    check(step(rp, col, w, op), graph.opinion_step(rp, col, w, op, 0.4, 0.5), lens)
+
+
+def test_tiles_many_edges():
+    lens = np.random.default_rng(2).integers(0, 28, 200_000)
+    lens[[100_000, 199_999]] = 64, 1500
+    rp, col, w, op = make(lens, seed=3)
+    assert rp[-1] >= 2_500_000 and 8.0 <= rp[-1] / 200_000 < 24.0
+    rows = np.unique(np.concatenate([[0, 100_000, 199_999],
+                                     np.random.default_rng(4).integers(0, 200_000, 2000)]))
+    check(step(rp, col, w, op)[rows], graph.opinion_step(rp, col, w, op, 0.4, 0.5, nodes=rows),
+          lens[rows])
+
+
+def test_tiles_bad_arrays():
+    """Targets outside [0, n) are skipped; a row_ptr that does not ascend, or leaves
+    [0, n_edges], is clamped row by row."""
+    n = 400
+    lens = np.random.default_rng(5).integers(0, 12, n)
+    rp, col, w, op = make(lens, seed=6)
+    bad = col.copy()
+    bad[::7], bad[3::11] = n, -3
+    ok = (bad >= 0) & (bad < n)
+    rp_ok = np.concatenate([[0], np.cumsum(ok)])[rp]
+    check(step(rp, bad, w, op), graph.opinion_step(rp_ok, bad[ok], w[ok], op, 0.4, 0.5), lens)
+    odd = rp.copy()
+    odd[5], odd[200], odd[201], odd[300] = 40, -9, rp[-1] + 50, 3   # the last block stays in order
+    got = step(odd, col, w, op)
+    want = graph.opinion_step(np.clip(odd, 0, rp[-1]), col, w, op, 0.4, 0.5)
+    check(got, want, np.zeros(n))                                    # edge by edge: bitwise
