@@ -250,11 +250,11 @@ int env_batch_get_sweep_lanes(const env_batch_t *b, int32_t *lanes);
  * the issue-bound sweep.  ENV_EINVAL for a NULL batch. */
 int env_batch_set_policy_fusion(env_batch_t *b, int on);
 
-/* Bound on the wait of the batch's strip sort (polling rounds; default
+/* Bound on the wait of the batch's strip sort (polls; default
  * 16384).  The sort cuts each env's grid columns into strips, one block each,
- * and a strip takes its first output row from the running totals of the
- * strips before it; a strip whose wait runs out counts the agents before it
- * itself.  Results are the same for every value: 0 makes every strip count
+ * and a strip takes its first output row from its own records and from the
+ * count of agents that crossed the box's edge, which the env's first strip
+ * publishes; a strip whose wait runs out counts the agents before it itself.  Results are the same for every value: 0 makes every such strip count
  * (the fallback, for tests).  Drops captured graphs when the value changes.
  * ENV_EINVAL for a NULL batch or polls < 0. */
 int env_batch_set_strip_wait(env_batch_t *b, int polls);

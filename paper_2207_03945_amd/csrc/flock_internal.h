@@ -77,11 +77,11 @@ struct SortArrays {
     int32_t *part;     // [scan partials]
     DevEnv *envs[2];   // [E] descriptor tables: [0] as stored, [1] buffers swapped
     int32_t *base;     // [E + 1] agent_base of each env, then G
-    // Strip sort (S strips): env of each strip, and the strips' look-back
-    // words then the block ticket counter (S + 1 words, zero between steps).
+    // Strip sort (S strips): env of each strip, and per env, at its first strip,
+    // the word with its edge crossings (S words, zero between steps).
     int32_t *strip_env;  // [S]
-    uint32_t *status;    // [S + 1]
-    int32_t n_status;    // S + 1 (0 without strips)
+    uint32_t *status;    // [S]
+    int32_t n_status;    // S (0 without strips)
 };
 
 // The shared policy evaluated inside a step's view sweep, on the view the
@@ -103,7 +103,7 @@ struct PolFuse {
 };
 
 // Launch plan of one step over a fixed set of envs.
-// Default bound on a strip's look-back wait, in polling rounds.
+// Default bound on a strip's wait for its env's edge crossings, in polls.
 constexpr int kStripWait = 1 << 14;
 
 struct StepPlan {
@@ -122,9 +122,8 @@ struct StepPlan {
     int strips;             // > 0: the envs' column strips (the strip sort is allowed)
     int strip_now;          // this launch may use the strip sort (every env's records sorted)
     int strip_cells;        // cells of the plan's largest strip
-    int strip_cap;          // agents a strip block lists in LDS (more: a second pass)
-    // polling rounds a strip waits for the running totals of the strips before
-    // it; when they run out it counts the agents before it itself (0: always)
+    // polls a strip makes for the edge crossings that its env's first strip
+    // counts; when they run out it counts the agents before it itself (0: always)
     int strip_wait = kStripWait;
 };
 
@@ -175,7 +174,8 @@ void carve_sort(Carver &cv, int64_t G, int64_t C, int E, SortArrays *a, int64_t 
 // Strip sort: one block per strip of columns of one env moves the agents of
 // its columns and of the two next to them (an agent moves at most one
 // column per step), keeps those now in its strip, ranks them by cell in LDS,
-// takes its output offset from the strips before it (look-back), and writes
+// takes its output offset from its own records and from the count of agents
+// that crossed the box's edge (the env's first strip publishes it), and writes
 // them in cell order with the strip's cell starts.  Allowed for an env when
 // its records are in cell order, its speed limit is at most half a column
 // and a strip's cells fit the block's LDS.
@@ -187,8 +187,7 @@ int strip_cols_for(const DevEnv &d, int64_t G);
 // strip_env with the env index of each strip.
 int64_t assign_strips(DevEnv *const *tabs, int n_tabs, int n_envs, int64_t G,
                       std::vector<int32_t> *strip_env);
-// Fill the plan's strip_cells / strip_cap from its envs'
-// descriptors (after assign_strips) and its strip count.
+// Fill the plan's strip_cells from its envs' descriptors (after assign_strips).
 void plan_strip_launch(StepPlan *p, const DevEnv *envs, int n_envs);
 
 // Launchers (return hipSuccess or the first error) ------------------------

@@ -601,31 +601,46 @@ __global__ __launch_bounds__(kEnvNT) void k_env_sort(SortArrays a, const DevEnv 
 
 // One block per strip of columns of one env (see carve_sort and the plan's
 // strips in flock_internal.h).  The records are in cell order (column
-// major), so the records of a range of columns are one range of records,
-// found by a search; an agent moves at most one column per step, so the
-// agents now in the strip were, before the move, in its columns or in the one
-// on either side.  The block moves those (twice: once to count, once to
-// place, reading the records again from cache instead of keeping a variable
-// number of them), ranks its agents by cell in LDS, takes its first output
-// row from the strips of the env before it by decoupled look-back, and
-// writes its agents in cell order and its cells' starts.
-constexpr int kStripNT = 512;
+// major), so the records of a range of columns are one range of records; an
+// agent moves at most one column per step, so the agents now in the strip
+// were, before the move, in its columns or in the one on either side.  The
+// block loads and moves those, ranks its agents by cell in LDS, and writes
+// them in cell order with the strip's cell starts.  The first NT * R records
+// stay in registers between counting and placing; a denser strip reads the
+// rest twice (the second time from cache).
+//
+// Where the strip's agents go: the agents now in columns below c0 are the
+// records before the block's range, plus those in its range that are now
+// below c0 -- all known to the block -- but for the agents that crossed the
+// box's periodic edge outside the range, either way.  The env's first strip
+// has both edge columns in its range and publishes the net count of those
+// crossings, one word, as soon as it has moved them; the last strip needs
+// only the env's size.  So no strip waits for any but the first, and none
+// where an env has at most two.
+//
+// What bounds it: a chain of dependent memory accesses (descriptor, ends of
+// the range, records, actions by id, stores), and for large plans the traffic
+// of about 80 bytes per agent with the records of the strips' neighbouring
+// columns on top.  So as few rounds as the registers allow: up to one block
+// per CU, 1024 threads of 4 records (10,000 agents in 9 strips: 3 us less than
+// with 512 threads); else 512 threads of 3, which four blocks per CU hold without
+// spilling (4 records, 3 blocks per CU: the same on uniform agents, steps 3 %
+// slower on clustered ones; 8 records or 256 threads: steps 3 to 25 % slower).
+// MI355X, against look-back over all strips of the env, tickets, and a list in
+// LDS instead of registers: 256 uneven envs of 0.96 M agents 38.6 -> 25.5 us, 20
+// clustered envs of 50,000 57.8 -> 42.2 (the densest strip: 5,800 of its 7,000
+// records), 16,000 agents in 20 strips 13.2 -> 11.0, 5,000 in 10 strips
+// 9.6 -> 7.7.
 constexpr int kXcds = 8;     // MI355X: accelerator dies (XCDs), each with its own L2
-constexpr int kStripR = 4;   // old records per thread and round (placing by a second pass)
-constexpr int kStripR1 = 4;  // old records per thread and round of the counting pass (8: no faster, 89 VGPRs)
-constexpr uint32_t kStripAgg = 1u << 30;   // look-back word: the strip's own count is set
-constexpr uint32_t kStripIncl = 1u << 31;  // the count of the env's strips up to this one is set
-constexpr uint32_t kStripVal = kStripAgg - 1;
-// Look-back waits are bounded (the plan's strip_wait polling rounds).  With
-// tickets a strip waits only for strips already running.  Without them (the
-// block index picks the strip) every block is meant to be resident at once,
-// which the runtime's occupancy figure suggests but nothing guarantees: a
-// strip whose wait runs out counts the agents before it itself
-// (strip_base_by_count), so the sort stays exact and the wait bounded.
+constexpr uint32_t kStripSet = 1u << 31;  // status word: the env's edge crossings are set
+// The wait for that word is bounded (the plan's strip_wait polls): the blocks of
+// one launch start in order, so it comes, but nothing guarantees it.  A strip
+// whose wait runs out counts the agents before it itself (strip_base_by_count),
+// so the sort stays exact and every block ends.
 
 // The env's agents that the step moves into columns below c0: every old
 // record of env E moved as in the strip sort (one wave, all of its lanes
-// calling).  The look-back's fallback, O(n) per call.
+// calling).  The fallback for a wait that ran out, O(n) per call.
 __device__ int strip_base_by_count(const DevEnv &E, int c0, int do_move,
                                    const float2 *__restrict__ act) {
     const int lane = threadIdx.x & 63;
@@ -646,185 +661,148 @@ __device__ int strip_base_by_count(const DevEnv &E, int c0, int do_move,
     return cnt;
 }
 
-// First record of env E (cell order) whose column is >= col; n when col >=
-// ncx.  Every lane of the calling wave takes part: each round probes 64
-// evenly spaced records of the remaining range (columns are nondecreasing, so
-// the probes below col form a prefix of the lanes).
-__device__ int wave_first_col(const DevEnv &E, int col) {
-    if (col <= 0) return 0;
-    if (col >= E.ncx) return E.n;
-    const int lane = threadIdx.x & 63;
-    int lo = 0, hi = E.n;  // the answer lies in [lo, hi]
-    while (lo < hi) {
-        const int step = (hi - lo + 63) >> 6;
-        const int q = lo + lane * step;
-        const bool below = q < hi && cell_of(E.rec_cur[q].x, E.inv_cx, E.ncx) < col;
-        const uint64_t m = __ballot(below);
-        const int k = m ? 64 - __builtin_clzll(m) : 0;  // probes below col
-        if (k == 0) break;                              // record lo is at or past col
-        const int next = lo + k * step;                 // first probe not below (or past hi)
-        lo = lo + (k - 1) * step + 1;
-        hi = next < hi ? next : hi;
-    }
-    return lo;
-}
-
-template <int NT>
-__global__ __launch_bounds__(NT) void k_strip_sort(SortArrays a, const DevEnv *__restrict__ envs,
-                                                   int n_envs, int C, int G, int S, int do_move,
-                                                   const float2 *__restrict__ act, int tag,
-                                                   float2 *__restrict__ act_copy, int cap,
-                                                   int direct, int wait) {
-    // dynamic LDS: the strip's cells (counts, then each cell's next free row),
-    // then up to `cap` of its agents: old record, cell, action
-    extern __shared__ int s_dyn[];
-    __shared__ int s_wave[NT / 64 + 1];
-    __shared__ int s_tk, s_base, s_own;
-    __shared__ int s_rng[4];
-    const int tid = threadIdx.x;
-    if (tid == 0) {
-        // With few strips every block is resident at once and the block index
-        // picks the strip: blocks go to the XCDs round robin, and XCD x takes
-        // the x-th run of `direct` consecutive strips, so an env's strips share
-        // one or two XCDs' L2 for their action gathers.  Otherwise a ticket
-        // makes strips start in order.
-        if (direct) {
-            const int x = (int)blockIdx.x % kXcds, k = (int)blockIdx.x / kXcds;
-            s_tk = k < direct ? x * direct + k : S;
-        } else {
-            s_tk = (int)atomicAdd(&a.status[S], 1u);
-        }
-        s_own = 0;
-    }
-    __syncthreads();
-    const int t = s_tk;
-    if (t >= S) return;  // a block past the last strip (direct mode padding)
+template <int NT, int R, int kWaves>
+__global__ __launch_bounds__(NT, kWaves) void k_strip_sort(
+    SortArrays a, const DevEnv *__restrict__ envs, int n_envs, int C, int G, int S, int do_move,
+    const float2 *__restrict__ act, int tag, float2 *__restrict__ act_copy, int per_xcd, int wait) {
+    extern __shared__ int s_cells[];  // the strip's cells: counts, then each cell's first row
+    __shared__ int s_wave[NT / 64 + 1], s_probe[NT / 64];
+    __shared__ int s_base, s_side;
+    const int tid = threadIdx.x, lane = tid & 63;
+    // Blocks go to the XCDs round robin: XCD x takes the x-th run of per_xcd
+    // consecutive strips, so an env's strips share one or two XCDs' L2.
+    const int t = (int)blockIdx.x % kXcds * per_xcd + (int)blockIdx.x / kXcds;
+    if (t >= S) return;  // a block past the last strip
     const DevEnv &E = envs[n_envs == 1 ? 0 : a.strip_env[t]];
     const int ls = t - E.strip_base, nst = E.n_strips, ncx = E.ncx, ncy = E.ncy, n = E.n;
     const int c0 = ls * E.strip_cols, c1 = ls == nst - 1 ? ncx : c0 + E.strip_cols;
     const int cbase = c0 * ncy, ncell = (c1 - c0) * ncy;
-    int *s_cells = s_dyn;
-    int *s_oi = s_dyn + ((ncell + 3) & ~3);
-    int *s_oc = s_oi + cap;
-    float2 *s_oa = reinterpret_cast<float2 *>(s_oc + cap);
     for (int c = tid; c < ncell; c += NT) s_cells[c] = 0;
-    // old records of columns c0 - 1 .. c1 (periodic): all of them when those
-    // columns cover the box, else one range or two (wrapping); waves 0 and 1
-    // search one boundary each
-    if (tid == 0) {
-        s_rng[0] = 0;
-        s_rng[1] = n;
-        s_rng[2] = 0;
-        s_rng[3] = 0;
-    }
-    __syncthreads();
-    if (nst > 1 && c1 - c0 + 2 < ncx && tid < 128) {
-        const int w = tid >> 6;
-        int col, slot;
-        if (c0 == 0) {
-            col = w == 0 ? ncx - 1 : c1 + 1;
-            slot = w == 0 ? 0 : 3;
-        } else if (c1 == ncx) {
-            col = w == 0 ? c0 - 1 : 1;
-            slot = w == 0 ? 0 : 3;
+    if (tid == 0) s_side = 0;
+    // A range of old records that holds those of columns c0 - 1 .. c1
+    // (periodic; two ranges where they wrap; all records when they cover the
+    // box).  Half the block's waves look for either end, one probe per lane
+    // at equal distances: columns are nondecreasing, so the probes below a
+    // column are the first ones, and the end is known to n / (NT / 2)
+    // records.  The few records too many fall to the column test below.
+    int r0 = 0, r1 = n, r2 = 0;  // [r0, r1) and then [0, r2)
+    const bool part = nst > 1 && c1 - c0 + 2 < ncx;
+    if (part) {
+        constexpr int P = NT / 2;
+        const int step = (n + P - 1) / P, half = tid / P, q = (tid - half * P) * step;
+        // first column of the range, first column past it
+        const int col = half == 0 ? (c0 == 0 ? ncx : c0) - 1 : (c1 == ncx ? 0 : c1) + 1;
+        const bool lower = q < n && cell_of(gload(E.rec_cur, q).x, E.inv_cx, ncx) < col;
+        const uint64_t m = __ballot(lower);
+        if (lane == 0) s_probe[tid >> 6] = __popcll(m);
+        __syncthreads();
+        int k0 = 0, k1 = 0;
+#pragma unroll
+        for (int w = 0; w < NT / 128; ++w) {
+            k0 += s_probe[w];
+            k1 += s_probe[NT / 128 + w];
+        }
+        k0 = __builtin_amdgcn_readfirstlane(k0);
+        k1 = __builtin_amdgcn_readfirstlane(k1);
+        const int lo = k0 > 0 ? (k0 - 1) * step + 1 : 0, hi = min(k1 * step, n);
+        if (c0 == 0 || c1 == ncx) {
+            if (lo > hi) r0 = lo, r2 = hi;  // else they meet: all records
         } else {
-            col = w == 0 ? c0 - 1 : c1 + 1;
-            slot = w == 0 ? 0 : 1;
+            r0 = lo;
+            r1 = max(hi, lo);
         }
-        const int r = wave_first_col(E, col);
-        if ((tid & 63) == 0) s_rng[slot] = r;
+    } else {
+        __syncthreads();
     }
-    __syncthreads();
-    // kStripR old records per thread and round, all loads issued before any
-    // is used (each record's action is a gather by its id); each record is
-    // moved as in k_env_sort
-    constexpr int R = kStripR;
-    auto round = [&](int i0, int i1, auto use) {
-        int id[R];
-        float4 m[R];
-        float2 av[R];
+    const int len = r1 - r0, total_old = len + r2;
+    auto index = [&](int v) { return v < len ? r0 + v : v - len; };
+    // the wave's count of records now below c0, edge crossings taken back; of
+    // the crossings, in minus out, in the first strip
+    int side = 0;
+    // NT * R old records from v0 on, all loads issued before any is used
+    // (each record's action is a gather by its id), each record moved as in
+    // k_env_sort; cell[u] < 0: not an agent of this strip
+    auto load_move = [&](int v0, int (&id)[R], float4 (&m)[R], float2 (&av)[R], int (&cell)[R],
+                         auto count) {
 #pragma unroll
         for (int u = 0; u < R; ++u) {
-            const int i = i0 + u * NT;
-            id[u] = i < i1 ? E.id_cur[i] : 0;
-            m[u] = i < i1 ? E.rec_cur[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            const int v = v0 + u * NT;
+            id[u] = 0;
+            m[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (v < total_old) {
+                const int i = index(v);
+                id[u] = gload(E.id_cur, i);
+                m[u] = gload(E.rec_cur, i);
+            }
         }
 #pragma unroll
         for (int u = 0; u < R; ++u) {
-            const int i = i0 + u * NT;
             av[u] = make_float2(0.0f, 0.0f);
-            if (do_move && i < i1 && (unsigned)id[u] < (unsigned)E.n)
-                av[u] = act ? act[E.agent_base + id[u]]
-                            : reinterpret_cast<const float2 *>(E.act)[id[u]];
+            if (do_move && v0 + u * NT < total_old && (unsigned)id[u] < (unsigned)n) {
+                typedef float gfloat2 __attribute__((ext_vector_type(2)));
+                const gfloat2 g = act ? ((const FLOCK_GLOBAL gfloat2 *)act)[E.agent_base + id[u]]
+                                      : ((const FLOCK_GLOBAL gfloat2 *)E.act)[id[u]];
+                av[u] = make_float2(g.x, g.y);
+            }
         }
 #pragma unroll
         for (int u = 0; u < R; ++u) {
-            const int i = i0 + u * NT;
-            if (i >= i1) continue;
-            const float4 mm = do_move ? move_record(E, m[u], av[u]) : m[u];
-            const int cx = cell_of(mm.x, E.inv_cx, ncx);
-            if (cx >= c0 && cx < c1)
-                use(i, mm, id[u], av[u], cx * ncy + cell_of(mm.y, E.inv_cy, ncy) - cbase);
-        }
-    };
-    auto each_old = [&](auto use) {
-        for (int r = 0; r < 4; r += 2)
-            for (int i0 = s_rng[r] + tid; i0 < s_rng[r + 1]; i0 += R * NT)
-                round(i0, s_rng[r + 1], use);
-    };
-    // pass 1: count the strip's agents per cell, listing the first `cap` of
-    // them (one LDS atomic per wave and record slot for the list position);
-    // kStripR1 records per thread and round
-    const int lane = tid & 63;
-    const uint64_t below = (1ull << lane) - 1ull;
-    constexpr int R1 = kStripR1;
-    for (int r = 0; r < 4; r += 2)
-        for (int i0 = s_rng[r] + tid; i0 < s_rng[r + 1]; i0 += R1 * NT) {
-            const int i1 = s_rng[r + 1];
-            int id[R1];
-            float4 m[R1];
-            float2 av[R1];
-#pragma unroll
-            for (int u = 0; u < R1; ++u) {
-                const int i = i0 + u * NT;
-                id[u] = i < i1 ? E.id_cur[i] : 0;
-                m[u] = i < i1 ? E.rec_cur[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            cell[u] = -1;
+            bool before = false, in = false, out = false;
+            if (v0 + u * NT < total_old) {
+                const int ox = cell_of(m[u].x, E.inv_cx, ncx);
+                if (do_move) m[u] = move_record(E, m[u], av[u]);
+                const int cx = cell_of(m[u].x, E.inv_cx, ncx);
+                if (cx >= c0 && cx < c1) cell[u] = cx * ncy + cell_of(m[u].y, E.inv_cy, ncy) - cbase;
+                in = part && ox == ncx - 1 && cx == 0;
+                out = part && ox == 0 && cx == ncx - 1;
+                before = out || (cx < c0 && !in);
             }
-#pragma unroll
-            for (int u = 0; u < R1; ++u) {
-                const int i = i0 + u * NT;
-                av[u] = make_float2(0.0f, 0.0f);
-                if (do_move && i < i1 && (unsigned)id[u] < (unsigned)E.n)
-                    av[u] = act ? act[E.agent_base + id[u]]
-                                : reinterpret_cast<const float2 *>(E.act)[id[u]];
-            }
-#pragma unroll
-            for (int u = 0; u < R1; ++u) {
-                const int i = i0 + u * NT;
-                int cell = -1;
-                if (i < i1) {
-                    const float4 mm = do_move ? move_record(E, m[u], av[u]) : m[u];
-                    const int cx = cell_of(mm.x, E.inv_cx, ncx);
-                    if (cx >= c0 && cx < c1) cell = cx * ncy + cell_of(mm.y, E.inv_cy, ncy) - cbase;
-                }
-                const uint64_t mask = __ballot(cell >= 0);
-                if (mask == 0) continue;
-                const int leader = __builtin_ctzll(mask);
-                int wbase = 0;
-                if (lane == leader) wbase = atomicAdd(&s_own, __popcll(mask));
-                wbase = __shfl(wbase, leader, 64);
-                if (cell >= 0) {
-                    atomicAdd(&s_cells[cell], 1);
-                    const int k = wbase + __popcll(mask & below);
-                    if (k < cap) {
-                        s_oi[k] = i;
-                        s_oc[k] = cell;
-                        s_oa[k] = av[u];
-                    }
-                }
+            if (count) {
+                if (ls == 0) side += __popcll(__ballot(in)) - __popcll(__ballot(out));
+                else side += __popcll(__ballot(before));
             }
         }
+    };
+    int id[R], cell[R], rank[R];
+    float4 m[R];
+    double ret[R];
+    {
+        float2 av[R];
+        load_move(tid, id, m, av, cell, std::true_type{});
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            rank[u] = 0;
+            ret[u] = 0.0;
+            if (cell[u] >= 0) {
+                ret[u] = gload(E.ret_cur, index(tid + u * NT));
+                rank[u] = atomicAdd(&s_cells[cell[u]], 1);
+                if (do_move && act_copy && (unsigned)id[u] < (unsigned)n)
+                    act_copy[E.agent_base + id[u]] = av[u];
+            }
+        }
+    }
+    // a denser strip's further records: counted now, placed by a second pass
+    const bool more = total_old > NT * R;
+    for (int v0 = NT * R + tid; v0 < total_old; v0 += NT * R) {
+        int id2[R], cell2[R];
+        float4 m2[R];
+        float2 av[R];
+        load_move(v0, id2, m2, av, cell2, std::true_type{});
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            if (cell2[u] >= 0) {
+                atomicAdd(&s_cells[cell2[u]], 1);
+                if (do_move && act_copy && (unsigned)id2[u] < (unsigned)n)
+                    act_copy[E.agent_base + id2[u]] = av[u];
+            }
+    }
+    if (lane == 0 && side != 0) atomicAdd(&s_side, side);
     __syncthreads();
+    uint32_t *const word = &a.status[E.strip_base];
+    if (ls == 0 && nst > 2 && tid == 0)
+        __hip_atomic_store(word, kStripSet | ((uint32_t)s_side & ~kStripSet), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     // exclusive scan of the counts: thread t owns cells [t k, t k + k)
     const int per = (ncell + NT - 1) / NT;
     const int q0 = tid * per;
@@ -838,47 +816,23 @@ __global__ __launch_bounds__(NT) void k_strip_sort(SortArrays a, const DevEnv *_
         run += cnt;
     }
     if (tid < 64) {
-        // the env's agents before this strip: decoupled look-back over the
-        // env's earlier strips, 64 of them per round (lane k reads strip
-        // t - 1 - k): the counts down to the nearest strip whose running total
-        // is set, once every one of them has published
-        uint32_t *st = a.status;
-        const int lane = tid;
+        // the env's agents before this strip
         int base = 0;
-        if (ls == 0) {
-            if (lane == 0)
-                __hip_atomic_store(&st[t], kStripIncl | (uint32_t)total, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            if (lane == 0)
-                __hip_atomic_store(&st[t], kStripAgg | (uint32_t)total, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            int top = t - 1, spins = 0;
-            while (spins < wait) {
-                const int j = top - lane;
-                const bool valid = j >= E.strip_base;
-                const uint32_t w = valid ? __hip_atomic_load(&st[j], __ATOMIC_RELAXED,
-                                                             __HIP_MEMORY_SCOPE_AGENT)
-                                         : 0u;
-                const uint64_t incl = __ballot(valid && (w & kStripIncl));
-                const uint64_t ready = __ballot(valid && (w & (kStripIncl | kStripAgg)));
-                const uint64_t need = incl ? (incl & (~incl + 1)) * 2 - 1  // lanes up to the nearest total
-                                           : __ballot(valid);
-                if ((ready & need) != need) {
-                    ++spins;
-                    continue;
+        if (ls == nst - 1) {
+            base = n - total;
+        } else if (ls > 0) {
+            base = s_side;
+            if (part) {
+                uint32_t w = 0;
+                int polls = 0;
+                while (polls < wait && !(w & kStripSet)) {
+                    w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    ++polls;
                 }
-                int v = ((need >> lane) & 1) ? (int)(w & kStripVal) : 0;
-#pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-                base += v;
-                if (incl) break;
-                top -= 64;
+                if (w & kStripSet) base += r0 + ((int)(w << 1) >> 1);
+                else base = strip_base_by_count(E, c0, do_move, act);
+                base = max(0, min(base, n - total));  // whatever the records hold
             }
-            if (spins >= wait) base = strip_base_by_count(E, c0, do_move, act);
-            if (lane == 0)
-                __hip_atomic_store(&st[t], kStripIncl | (uint32_t)(base + total), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
         }
         if (lane == 0) {
             s_base = base;
@@ -888,50 +842,32 @@ __global__ __launch_bounds__(NT) void k_strip_sort(SortArrays a, const DevEnv *_
     __syncthreads();
     const int base = s_base;
     for (int c = tid; c < ncell; c += NT) a.start[E.cell_base + cbase + c] = E.agent_base + base + s_cells[c];
-    __syncthreads();  // the starts are read before the counts become row cursors
-    // place the strip's agents: from the list (one load round: record, id,
-    // return), or, when the strip holds more than `cap`, by a second pass
-    auto place = [&](int i, const float4 &m, int id, float2 av, int cell) {
-        const int j = base + atomicAdd(&s_cells[cell], 1);
-        E.rec_nxt[j] = m;
-        E.id_nxt[j] = id;
-        E.ret_nxt[j] = E.ret_cur[i];
-        a.sxy[E.agent_base + j] = make_float2(m.x, m.y);
-        if (tag) a.stype[E.agent_base + j] = id < E.n_chasers ? 1 : 0;
-        if (do_move && act_copy && (unsigned)id < (unsigned)E.n) act_copy[E.agent_base + id] = av;
+    auto put = [&](int j, const float4 &r, int who, double sum_ret) {
+        ((FLOCK_GLOBAL gfloat4 *)E.rec_nxt)[j] = gfloat4{r.x, r.y, r.z, r.w};
+        gstore(E.id_nxt, j, who);
+        gstore(E.ret_nxt, j, sum_ret);
+        a.sxy[E.agent_base + j] = make_float2(r.x, r.y);
+        if (tag) a.stype[E.agent_base + j] = who < E.n_chasers ? 1 : 0;
     };
-    const int own = s_own;
-    if (own <= cap) {
-        for (int k0 = tid; k0 < own; k0 += R * NT) {
-            int oi[R], id[R];
-            float4 m[R];
-            double ret[R];
+    if (!more) {
 #pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const int k = k0 + u * NT;
-                oi[u] = k < own ? s_oi[k] : 0;
-                id[u] = k < own ? E.id_cur[oi[u]] : 0;
-                m[u] = k < own ? E.rec_cur[oi[u]] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                ret[u] = k < own ? E.ret_cur[oi[u]] : 0.0;
-            }
+        for (int u = 0; u < R; ++u)
+            if (cell[u] >= 0) put(base + s_cells[cell[u]] + rank[u], m[u], id[u], ret[u]);
+        return;
+    }
+    __syncthreads();  // the starts are read before they become row cursors
 #pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const int k = k0 + u * NT;
-                if (k >= own) continue;
-                const float2 av = s_oa[k];
-                const float4 mm = do_move ? move_record(E, m[u], av) : m[u];
-                const int j = base + atomicAdd(&s_cells[s_oc[k]], 1);
-                E.rec_nxt[j] = mm;
-                E.id_nxt[j] = id[u];
-                E.ret_nxt[j] = ret[u];
-                a.sxy[E.agent_base + j] = make_float2(mm.x, mm.y);
-                if (tag) a.stype[E.agent_base + j] = id[u] < E.n_chasers ? 1 : 0;
-                if (do_move && act_copy && (unsigned)id[u] < (unsigned)E.n)
-                    act_copy[E.agent_base + id[u]] = av;
-            }
-        }
-    } else {
-        each_old(place);
+    for (int u = 0; u < R; ++u)
+        if (cell[u] >= 0) put(base + atomicAdd(&s_cells[cell[u]], 1), m[u], id[u], ret[u]);
+    for (int v0 = NT * R + tid; v0 < total_old; v0 += NT * R) {
+        float2 av[R];
+        load_move(v0, id, m, av, cell, std::false_type{});
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            if (cell[u] >= 0) ret[u] = gload(E.ret_cur, index(v0 + u * NT));
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            if (cell[u] >= 0) put(base + atomicAdd(&s_cells[cell[u]], 1), m[u], id[u], ret[u]);
     }
 }
 
@@ -1584,7 +1520,7 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
     int *s_pe = reinterpret_cast<int *>(s_min + PL.env);
     int *s_pid = reinterpret_cast<int *>(s_min + PL.id);
     if constexpr (kPol != 0) load_pol_consts(pf.P, s_pc, tid, NT);
-    // the strip sort's look-back words and ticket, zero again for the next step
+    // the strip sort's words, zero again for the next step
     if (blockIdx.x == 0)
         for (int i = tid; i < a.n_status; i += NT) a.status[i] = 0u;
     if constexpr (G == 1 || kPol != 0) __syncthreads();
@@ -2033,8 +1969,8 @@ void carve_sort(Carver &cv, int64_t G, int64_t C, int E, SortArrays *a, int64_t 
     a->envs[1] = cv.take<DevEnv>(E);
     a->base = cv.take<int32_t>(E + 1);
     a->strip_env = S > 0 ? cv.take<int32_t>(S) : nullptr;
-    a->status = S > 0 ? cv.take<uint32_t>(S + 1) : nullptr;
-    a->n_status = S > 0 ? (int32_t)(S + 1) : 0;
+    a->status = S > 0 ? cv.take<uint32_t>(S) : nullptr;
+    a->n_status = S > 0 ? (int32_t)S : 0;
 }
 
 bool strips_allowed(const DevEnv &d) {
@@ -2053,48 +1989,10 @@ int strip_cols_for(const DevEnv &d, int64_t G) {
     return std::min(cols, d.ncx);
 }
 
-// LDS of a strip block: cells, then 16 bytes per listed agent.
-static size_t strip_lds_bytes(int cells, int cap) {
-    return ((size_t)((cells + 3) & ~3) + 4 * (size_t)cap) * sizeof(int);
-}
-
 void plan_strip_launch(StepPlan *p, const DevEnv *envs, int n_envs) {
     int cells = 1;
-    double own = 1.0;
-    for (int e = 0; e < n_envs; ++e) {
-        const DevEnv &d = envs[e];
-        cells = std::max(cells, d.strip_cols * d.ncy);
-        own = std::max(own, (double)std::max(d.n, 1) / d.ncx * d.strip_cols);
-    }
-    // half again the largest expected strip (uniform density), within 64 KiB
-    const int fit = (int)((65536 / sizeof(int) - ((cells + 3) & ~3)) / 4);
+    for (int e = 0; e < n_envs; ++e) cells = std::max(cells, envs[e].strip_cols * envs[e].ncy);
     p->strip_cells = cells;
-    p->strip_cap = std::max(0, std::min((int)std::ceil(1.5 * own), fit));
-}
-
-// Whether every block of the plan's strip sort is resident at once (as the
-// runtime's occupancy calculation for this kernel and LDS size says), so the
-// block index can serve as the strip: a strip then only ever waits for
-// strips that are running.  The CU count is read once per device.
-static int strip_direct(const StepPlan &p) {
-    static int cus_of[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-    if (cus_of[dev] == 0) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            cus <= 0)
-            return 0;
-        cus_of[dev] = cus;
-    }
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void *>(k_strip_sort<kStripNT>), kStripNT,
-            strip_lds_bytes(p.strip_cells, p.strip_cap)) != hipSuccess)
-        return 0;
-    // the padded grid (a multiple of kXcds blocks) must be resident too
-    const int64_t blocks = (p.strips + kXcds - 1) / kXcds * kXcds;
-    return blocks <= (int64_t)cus_of[dev] * per_cu ? 1 : 0;
 }
 
 int64_t assign_strips(DevEnv *const *tabs, int n_tabs, int n_envs, int64_t G,
@@ -2201,15 +2099,18 @@ hipError_t launch_phase(const StepPlan &p, int table, StepPhase phase, int do_mo
     switch (phase) {
         case kPhaseMove:
             if (p.env_sort_recs == 0 && p.strips > 0 && p.strip_now) {
-                // direct: strips per XCD (blocks = kXcds x that, the last few idle)
-                const int per_xcd = strip_direct(p) ? (int)((p.strips + kXcds - 1) / kXcds) : 0;
-                const unsigned nblk = per_xcd ? (unsigned)(per_xcd * kXcds) : (unsigned)p.strips;
-                hipLaunchKernelGGL(k_strip_sort<kStripNT>, dim3(nblk), dim3(kStripNT),
-                                   strip_lds_bytes(p.strip_cells, p.strip_cap), s, p.a, envs,
-                                   p.n_envs, C, G, (int)p.strips, do_move,
-                                   reinterpret_cast<const float2 *>(act), p.tag,
-                                   reinterpret_cast<float2 *>(act_copy), p.strip_cap, per_xcd,
-                                   p.strip_wait);
+                const int per_xcd = (int)((p.strips + kXcds - 1) / kXcds);
+                auto go = [&](auto nt, auto r, auto waves) {
+                    constexpr int NT = decltype(nt)::value, R = decltype(r)::value;
+                    hipLaunchKernelGGL((k_strip_sort<NT, R, decltype(waves)::value>), dim3((unsigned)(per_xcd * kXcds)),
+                                       dim3(NT), (size_t)p.strip_cells * sizeof(int), s, p.a, envs,
+                                       p.n_envs, C, G, (int)p.strips, do_move,
+                                       reinterpret_cast<const float2 *>(act), p.tag,
+                                       reinterpret_cast<float2 *>(act_copy), per_xcd, p.strip_wait);
+                };
+                // one block per CU: latency; more: see the kernel
+                if (p.strips <= 256) go(std::integral_constant<int, 1024>{}, std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+                else go(std::integral_constant<int, 512>{}, std::integral_constant<int, 3>{}, std::integral_constant<int, 8>{});
                 break;
             }
             if (p.env_sort_recs > 0) {

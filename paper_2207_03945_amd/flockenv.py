@@ -330,8 +330,8 @@ class Batch:
         check(lib().env_batch_set_policy_fusion(self.handle, 1 if on else 0))
 
     def set_strip_wait(self, polls: int):
-        """Bound on the strip sort's look-back wait (polling rounds; 0: every
-        strip counts the agents before it itself).  Results do not depend on it."""
+        """Bound on the strip sort's wait for an env's edge crossings (polls; 0:
+        the waiting strips count the agents before them themselves).  Results do not depend on it."""
         check(lib().env_batch_set_strip_wait(self.handle, int(polls)))
 
     @property
