@@ -102,11 +102,12 @@ __device__ __forceinline__ int wave_max(int x) {
 // read from memory is generic to the compiler, and it waits on generic
 // accesses conservatively (they count as both vector-memory and LDS
 // operations).  These access such arrays through the global address space.
-// The sweep uses them where lane groups share an agent (its per-agent loads
-// and stores then overlap better: 245 -> 230 us for 50k-agent blobs at four
-// lanes); with one lane per agent the generic form measured faster.
+// The sorts use them, and the sweep where lane groups share an agent (its
+// per-agent loads and stores then overlap better: 245 -> 230 us for 50k-agent
+// blobs at four lanes); with one lane per agent the generic form measured faster.
 #define FLOCK_GLOBAL __attribute__((address_space(1)))
 typedef float gfloat4 __attribute__((ext_vector_type(4)));
+typedef float gfloat2 __attribute__((ext_vector_type(2)));
 
 template <class T>
 __device__ __forceinline__ T gload(const T *p, int64_t i) {
@@ -116,6 +117,11 @@ __device__ __forceinline__ T gload(const T *p, int64_t i) {
 __device__ __forceinline__ float4 gload(const float4 *p, int64_t i) {
     const gfloat4 v = ((const FLOCK_GLOBAL gfloat4 *)p)[i];
     return make_float4(v.x, v.y, v.z, v.w);
+}
+
+__device__ __forceinline__ float2 gload(const float2 *p, int64_t i) {
+    const gfloat2 v = ((const FLOCK_GLOBAL gfloat2 *)p)[i];
+    return make_float2(v.x, v.y);
 }
 
 template <class T>
@@ -507,6 +513,12 @@ __global__ __launch_bounds__(kScan2NT) void k_scan_down(int32_t *__restrict__ co
 // thread; the env's cell counts, then starts, live in dynamic LDS.  Up to
 // kEnvRegR records per thread the moved records and ids wait in registers
 // for the scatter; above that they are staged in `tmp`.
+// What bounds it: the addresses of the scattered stores and of the action
+// gather (the texture addresser is busy 22,000 of 37,000 cycles per CU at
+// 200 envs of 5,000), with one block per CU.  Measured there, us per step, 68.0
+// as it stands: records staged in LDS and stored in order 73 to 75; all loads of
+// a thread's records issued first 68.0; two blocks of 512 threads per CU 71.4;
+// the strip sort 74 to 75; generic instead of global loads and stores 68.8.
 constexpr int kEnvNT = 1024;
 constexpr int kEnvRegR = 8;
 
@@ -534,12 +546,12 @@ __global__ __launch_bounds__(kEnvNT) void k_env_sort(SortArrays a, const DevEnv 
         key[r] = 0;
         rank[r] = 0;
         if (i < n) {
-            float4 m = E.rec_cur[i];
-            const int id = E.id_cur[i];
+            float4 m = gload(E.rec_cur, i);
+            const int id = gload(E.id_cur, i);
             if (do_move) {
                 float2 av = make_float2(0.0f, 0.0f);
                 if ((unsigned)id < (unsigned)n) {  // ids are agent indices (a guard)
-                    av = act ? act[base + id] : reinterpret_cast<const float2 *>(E.act)[id];
+                    av = act ? act[base + id] : gload(reinterpret_cast<const float2 *>(E.act), id);
                     if (act_copy) act_copy[base + id] = av;
                 }
                 m = move_record(E, m, av);
@@ -547,7 +559,7 @@ __global__ __launch_bounds__(kEnvNT) void k_env_sort(SortArrays a, const DevEnv 
             if constexpr (kRegs) {
                 mr[r] = m;
                 idr[r] = id;
-                retr[r] = E.ret_cur[i];  // loaded now, stored after the scan
+                retr[r] = gload(E.ret_cur, i);  // loaded now, stored after the scan
             } else {
                 a.tmp[base + i] = m;
             }
@@ -585,12 +597,12 @@ __global__ __launch_bounds__(kEnvNT) void k_env_sort(SortArrays a, const DevEnv 
                 ret = retr[r];
             } else {
                 m = a.tmp[base + i];
-                id = E.id_cur[i];
-                ret = E.ret_cur[i];
+                id = gload(E.id_cur, i);
+                ret = gload(E.ret_cur, i);
             }
-            E.rec_nxt[j] = m;
-            E.id_nxt[j] = id;
-            E.ret_nxt[j] = ret;
+            ((FLOCK_GLOBAL gfloat4 *)E.rec_nxt)[j] = gfloat4{m.x, m.y, m.z, m.w};
+            gstore(E.id_nxt, j, id);
+            gstore(E.ret_nxt, j, ret);
             a.sxy[base + j] = make_float2(m.x, m.y);
             if (tag) a.stype[base + j] = id < E.n_chasers ? 1 : 0;
         }
@@ -739,10 +751,8 @@ __global__ __launch_bounds__(NT, kWaves) void k_strip_sort(
         for (int u = 0; u < R; ++u) {
             av[u] = make_float2(0.0f, 0.0f);
             if (do_move && v0 + u * NT < total_old && (unsigned)id[u] < (unsigned)n) {
-                typedef float gfloat2 __attribute__((ext_vector_type(2)));
-                const gfloat2 g = act ? ((const FLOCK_GLOBAL gfloat2 *)act)[E.agent_base + id[u]]
-                                      : ((const FLOCK_GLOBAL gfloat2 *)E.act)[id[u]];
-                av[u] = make_float2(g.x, g.y);
+                av[u] = act ? gload(act, E.agent_base + id[u])
+                            : gload(reinterpret_cast<const float2 *>(E.act), id[u]);
             }
         }
 #pragma unroll
