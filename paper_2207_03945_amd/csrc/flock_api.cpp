@@ -226,7 +226,6 @@ struct flock_env {
     StepPlan plan;          // its own step: a batch of one
     DevEnv scalars;         // descriptor without buffer pointers
     DevEnv own[2];          // own tables: [b] has buffer b current
-    int32_t base_host[2];   // {0, n}
     int parity = 0;         // index of the current record buffer
     uint64_t gen = 0;       // bumped by every call that changes the state
     bool sorted = false;    // records in cell order (after a sort; not after set_state)
@@ -250,15 +249,7 @@ DevEnv orient(const env_t *e, int cur) {
 
 int upload_own(env_t *e, hipStream_t s) {
     if (e->uploaded) return ENV_OK;
-    hipError_t err = hipMemcpyAsync(e->lay.sort.envs[0], &e->own[0], sizeof(DevEnv),
-                                    hipMemcpyHostToDevice, s);
-    if (err == hipSuccess)
-        err = hipMemcpyAsync(e->lay.sort.envs[1], &e->own[1], sizeof(DevEnv),
-                             hipMemcpyHostToDevice, s);
-    if (err == hipSuccess)
-        err = hipMemcpyAsync(e->lay.sort.base, e->base_host, sizeof(e->base_host),
-                             hipMemcpyHostToDevice, s);
-    if (err == hipSuccess) err = launch_clear(e->plan, s);
+    const hipError_t err = launch_bind_one(e->plan, e->own[0], e->own[1], e->p.n_agents, s);
     if (err != hipSuccess) return hip_fail(err, "env descriptor upload");
     e->uploaded = true;
     return ENV_OK;
@@ -357,8 +348,7 @@ void env_advance(env_t *env, int steps) {
 
 bool env_sorted(const env_t *env) { return env->sorted; }
 
-int env_load_host_state(env_t *env, const float *x, const float *y, const float *th,
-                        const float *s_, hipStream_t s) {
+int env_load_host_state(env_t *env, const float *state, hipStream_t s) {
     const int n = env->p.n_agents;
     env->has_state = true;
     env->sorted = false;
@@ -367,11 +357,7 @@ int env_load_host_state(env_t *env, const float *x, const float *y, const float 
     // Stage the agent-order arrays in the next buffer's record area (free
     // until the next step) and load them into the current buffer.
     float *stage = reinterpret_cast<float *>(env->lay.rec[env->parity ^ 1]);
-    const size_t b = (size_t)n * sizeof(float);
-    hipError_t e = hipMemcpyAsync(stage, x, b, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(stage + n, y, b, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(stage + 2 * (size_t)n, th, b, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(stage + 3 * (size_t)n, s_, b, hipMemcpyHostToDevice, s);
+    hipError_t e = hipMemcpyAsync(stage, state, 4 * (size_t)n * sizeof(float), hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = launch_load_state(stage, stage + n, stage + 2 * (size_t)n, stage + 3 * (size_t)n,
                               env->lay.rec[env->parity], env->lay.id[env->parity], n, s);
@@ -469,8 +455,6 @@ int env_create(const env_params_t *p, void *workspace, size_t bytes, env_t **out
     }
     e->own[0] = orient(e, 0);
     e->own[1] = orient(e, 1);
-    e->base_host[0] = 0;
-    e->base_host[1] = p->n_agents;
     e->plan.a = e->lay.sort;
     e->plan.n_envs = 1;
     e->plan.G = p->n_agents;

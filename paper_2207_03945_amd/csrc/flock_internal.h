@@ -255,9 +255,9 @@ const env_params_t &env_params(const env_t *env);
 int env_parity(const env_t *env);
 void env_advance(env_t *env, int steps);        // record `steps` stepped elsewhere
 bool env_sorted(const env_t *env);              // records in cell order (strip sort allowed)
-// Copy a host state into the env (async on s; host arrays must outlive the copy).
-int env_load_host_state(env_t *env, const float *x, const float *y, const float *th,
-                        const float *s_, hipStream_t s);
+// Copy a host state, x, y, th and s one after the other, into the env (async on
+// s; the host array must outlive the copy).
+int env_load_host_state(env_t *env, const float *state, hipStream_t s);
 // Device FP64 returns of the env in agent order, into `out` (device [n]).
 int env_returns_to(env_t *env, double *out, hipStream_t s);
 // Bytes of the batch sort scratch for G agents, C cells, E envs, S strips.
