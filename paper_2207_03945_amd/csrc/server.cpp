@@ -229,6 +229,13 @@ int try_admit(srv_t *S, Request &r) {
 // each, ordered on the host, four copies per initial state and three per
 // descriptor; 2.90 with this, one copy per state and descriptors by value.
 hipError_t download_returns(srv_t *S, const std::vector<Request *> &reqs) {
+    if (!S->pinned) {  // at the first retirement: a tick waits for its stream anyway
+        void *pin = nullptr;
+        if (hipHostMalloc(&pin, kPinnedReturns * sizeof(double), hipHostMallocDefault) == hipSuccess)
+            S->pinned = static_cast<double *>(pin);
+        else
+            (void)hipGetLastError();  // the returns then come down to pageable memory
+    }
     for (Request *r : reqs) {
         r->ret.resize(r->p.n_agents);
         const DevEnv d = env_descriptor(r->env, 0);
@@ -385,11 +392,6 @@ int srv_create(void *arena, size_t arena_bytes, int max_slots, pol_t *pol, void 
     S->pol = pol;
     S->stream = reinterpret_cast<hipStream_t>(stream);
     S->alloc.reset(arena_bytes);
-    void *pin = nullptr;
-    if (hipHostMalloc(&pin, kPinnedReturns * sizeof(double), hipHostMallocDefault) == hipSuccess)
-        S->pinned = static_cast<double *>(pin);
-    else
-        (void)hipGetLastError();  // the returns then come down to pageable memory
     *out = S;
     return ENV_OK;
 }
