@@ -273,12 +273,13 @@ __global__ __launch_bounds__(kTileNodes) void k_opinion_tile(int64_t n, int64_t 
 // 30,000 nodes where 4 lanes take 14 to 60 (the longest row's chain), even rows the
 // same up to 30,000 nodes and at 1M, 5 to 10 % more at 100,000 to 300,000.
 // From 8 to 24, tiles once there are edges enough to keep every CU at work through
-// both phases of a tile: 200,000 nodes of mean degree 14 (2.8 M edges) take 37 us
-// with 16 lanes and 34 with tiles, 100,000 take 24 and 32, 300,000 even rows
-// of 8 (2.4 M) 15.5 and 15.9.  Above, a lane's share of a row fills its slots:
+// both phases of a tile: 300,000 power-law rows of 8 (2.5 M edges) take 44 us with 16
+// lanes and 27 with tiles, even rows of 8 (2.4 M) 15.5 and 15.9, 200,000 rows of
+// 14 (2.8 M) 37 and 34, but 150,000 (2.1 M) 32 and 33 and 100,000 24 and 32.
+// Above, a lane's share of a row fills its slots:
 // 300,000 rows of 30 take 50 us with 16 lanes and 53 with tiles, of 48, 72 and 130.
 bool graph_use_tiles(int64_t n_edges, double mean_degree) {
-    return mean_degree >= 3.0 && (mean_degree < 8.0 || (mean_degree < 24.0 && n_edges >= 2500000));
+    return mean_degree >= 3.0 && (mean_degree < 8.0 || (mean_degree < 24.0 && n_edges >= 2300000));
 }
 
 // Lanes per node for the rest, from the mean degree: power-law rows are uneven,

@@ -1,5 +1,5 @@
 """GPU graph interaction where the lanes per node are left to the library and it
-takes tiles of edges (mean degree 3 to 8, or up to 24 with 2.5 M edges).
+takes tiles of edges (mean degree 3 to 8, or up to 24 with 2.3 M edges).
 
 A node whose edges in a tile number less than 64 applies them one by one in FP64,
 so its FP32 output is bitwise the oracle's rounded result; longer rows compose
