@@ -270,7 +270,8 @@ struct flock_batch {
     std::vector<DevEnv> tab[2];      // [t]: env k has buffer base_par[k] ^ t current
     std::vector<int32_t> base;
     std::vector<int64_t> off;
-    std::vector<int32_t> strip_env;  // env of each strip (strip sort)
+    std::vector<int32_t> strips_of;  // strips of each env (strip sort)
+    std::vector<int32_t> strip_env;  // env of each strip in launch order
     StepPlan plan;
     bool uploaded = false;
     GraphCache gc[2];                // K-step graphs by starting table
@@ -695,14 +696,14 @@ static int batch_layout(env_t *const *envs, int n_envs, std::vector<int32_t> *ba
 
 // Strips of a batch's envs (the strip sort), 0 when some env does not allow it.
 static int64_t batch_strips(env_t *const *envs, int n_envs, int64_t G,
-                            std::vector<int32_t> *strip_env) {
+                            std::vector<int32_t> *strips_of) {
     std::vector<DevEnv> d(n_envs);
     for (int k = 0; k < n_envs; ++k) {
         d[k] = envs[k]->scalars;
         if (!strips_allowed(d[k])) return 0;
     }
     DevEnv *tabs[1] = {d.data()};
-    return assign_strips(tabs, 1, n_envs, G, strip_env);
+    return assign_strips(tabs, 1, n_envs, G, strips_of);
 }
 
 size_t env_batch_workspace_bytes(env_t *const *envs, int n_envs) {
@@ -743,7 +744,7 @@ int env_batch_create(env_t *const *envs, int n_envs, void *ws, size_t bytes, env
         }
     }
     Carver cv{static_cast<char *>(ws), 0};
-    const int64_t S = batch_strips(envs, n_envs, G, &b->strip_env);
+    const int64_t S = batch_strips(envs, n_envs, G, &b->strips_of);
     carve_sort(cv, G, C, n_envs, &b->plan.a, S);
     b->act_next = cv.take<float2>((size_t)G);
     if (bytes < align_up(cv.off, 256)) {
@@ -873,9 +874,11 @@ static int batch_prepare(env_batch_t *b, hipStream_t s, int *table) {
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->plan.a.base, b->base.data(), b->base.size() * sizeof(int32_t),
                            hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && !b->uploaded && b->plan.strips > 0)
+    if (e == hipSuccess && !b->uploaded && b->plan.strips > 0) {
+        b->strip_env = strip_launch_order(&b->plan, b->strips_of);
         e = hipMemcpyAsync(b->plan.a.strip_env, b->strip_env.data(),
                            b->strip_env.size() * sizeof(int32_t), hipMemcpyHostToDevice, s);
+    }
     if (e == hipSuccess && !b->uploaded) e = launch_clear(b->plan, s);
     if (e != hipSuccess) return hip_fail(e, "batch upload");
     b->uploaded = true;

@@ -77,8 +77,8 @@ struct SortArrays {
     int32_t *part;     // [scan partials]
     DevEnv *envs[2];   // [E] descriptor tables: [0] as stored, [1] buffers swapped
     int32_t *base;     // [E + 1] agent_base of each env, then G
-    // Strip sort (S strips): env of each strip, and per env, at its first strip,
-    // the word with its edge crossings (S words, zero between steps).
+    // Strip sort (S strips): env of each strip in launch order, and per env, at
+    // its first strip, the word with its edge crossings (S words, zero between steps).
     int32_t *strip_env;  // [S]
     uint32_t *status;    // [S]
     int32_t n_status;    // S (0 without strips)
@@ -120,6 +120,7 @@ struct StepPlan {
     int64_t max_env_cells;  // cells of the plan's largest env
     int env_sort_recs;      // > 0: one block per env does move to scatter (records per thread)
     int strips;             // > 0: the envs' column strips (the strip sort is allowed)
+    int strips_ahead = 0;   // envs' first strips at the head of the launch (strip_order.h)
     int strip_now;          // this launch may use the strip sort (every env's records sorted)
     int strip_cells;        // cells of the plan's largest strip
     // polls a strip makes for the edge crossings that its env's first strip
@@ -184,9 +185,12 @@ bool strips_allowed(const DevEnv &d);
 // Strip width of an env for a plan of G agents in all: columns per strip.
 int strip_cols_for(const DevEnv &d, int64_t G);
 // Assign strips to the envs' descriptors (in order); returns S and fills
-// strip_env with the env index of each strip.
+// strips_of with the strips of each env.
 int64_t assign_strips(DevEnv *const *tabs, int n_tabs, int n_envs, int64_t G,
-                      std::vector<int32_t> *strip_env);
+                      std::vector<int32_t> *strips_of);
+// Choose the plan's launch order of its strips (strip_order.h) for the current
+// device; returns the env of each strip in that order, the plan's strip_env.
+std::vector<int32_t> strip_launch_order(StepPlan *p, const std::vector<int32_t> &strips_of);
 // Fill the plan's strip_cells from its envs' descriptors (after assign_strips).
 void plan_strip_launch(StepPlan *p, const DevEnv *envs, int n_envs);
 

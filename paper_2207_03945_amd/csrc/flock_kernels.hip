@@ -41,11 +41,13 @@
 #include <limits.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 
 #include <type_traits>
 
 #include "flock_internal.h"
+#include "strip_order.h"
 
 namespace flock {
 
@@ -643,12 +645,12 @@ __global__ __launch_bounds__(kEnvNT) void k_env_sort(SortArrays a, const DevEnv 
 // clustered envs of 50,000 57.8 -> 42.2 (the densest strip: 5,800 of its 7,000
 // records), 16,000 agents in 20 strips 13.2 -> 11.0, 5,000 in 10 strips
 // 9.6 -> 7.7.
-constexpr int kXcds = 8;     // MI355X: accelerator dies (XCDs), each with its own L2
 constexpr uint32_t kStripSet = 1u << 31;  // status word: the env's edge crossings are set
-// The wait for that word is bounded (the plan's strip_wait polls): the blocks of
-// one launch start in order, so it comes, but nothing guarantees it.  A strip
-// whose wait runs out counts the agents before it itself (strip_base_by_count),
-// so the sort stays exact and every block ends.
+// The wait for that word is bounded (the plan's strip_wait polls).  The first
+// strips run at once with the strips that wait for them or come before them in
+// the launch (strip_order.h), so the word comes where blocks start in order, but
+// nothing guarantees that.  A strip whose wait runs out counts the agents before
+// it itself (strip_base_by_count), so the sort stays exact and every block ends.
 
 // The env's agents that the step moves into columns below c0: every old
 // record of env E moved as in the strip sort (one wave, all of its lanes
@@ -673,20 +675,21 @@ __device__ int strip_base_by_count(const DevEnv &E, int c0, int do_move,
     return cnt;
 }
 
-template <int NT, int R, int kWaves>
+template <int NT, int R, int kWaves, bool kAhead>
 __global__ __launch_bounds__(NT, kWaves) void k_strip_sort(
     SortArrays a, const DevEnv *__restrict__ envs, int n_envs, int C, int G, int S, int do_move,
-    const float2 *__restrict__ act, int tag, float2 *__restrict__ act_copy, int per_xcd, int wait) {
+    const float2 *__restrict__ act, int tag, float2 *__restrict__ act_copy, int run_len, int wait) {
     extern __shared__ int s_cells[];  // the strip's cells: counts, then each cell's first row
     __shared__ int s_wave[NT / 64 + 1], s_probe[NT / 64];
     __shared__ int s_base, s_side;
     const int tid = threadIdx.x, lane = tid & 63;
-    // Blocks go to the XCDs round robin: XCD x takes the x-th run of per_xcd
-    // consecutive strips, so an env's strips share one or two XCDs' L2.
-    const int t = (int)blockIdx.x % kXcds * per_xcd + (int)blockIdx.x / kXcds;
-    if (t >= S) return;  // a block past the last strip
-    const DevEnv &E = envs[n_envs == 1 ? 0 : a.strip_env[t]];
-    const int ls = t - E.strip_base, nst = E.n_strips, ncx = E.ncx, ncy = E.ncy, n = E.n;
+    const int ahead = kAhead ? n_envs : 0;
+    const int place = strip_place(blockIdx.x, ahead, run_len);
+    if (place >= S) return;  // a block past the last strip
+    const int e = n_envs == 1 ? 0 : a.strip_env[place];
+    const DevEnv &E = envs[e];
+    const int ls = strip_in_env(place, ahead, e, E.strip_base);
+    const int nst = E.n_strips, ncx = E.ncx, ncy = E.ncy, n = E.n;
     const int c0 = ls * E.strip_cols, c1 = ls == nst - 1 ? ncx : c0 + E.strip_cols;
     const int cbase = c0 * ncy, ncell = (c1 - c0) * ncy;
     for (int c = tid; c < ncell; c += NT) s_cells[c] = 0;
@@ -846,7 +849,7 @@ __global__ __launch_bounds__(NT, kWaves) void k_strip_sort(
         }
         if (lane == 0) {
             s_base = base;
-            if (t == S - 1) a.start[C] = G;
+            if (blockIdx.x == 0) a.start[C] = G;
         }
     }
     __syncthreads();
@@ -1999,6 +2002,30 @@ int strip_cols_for(const DevEnv &d, int64_t G) {
     return std::min(cols, d.ncx);
 }
 
+// CUs of the current device, read once per device.
+static int device_cus() {
+    static std::atomic<int> known[64];
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    cus = known[dev].load(std::memory_order_relaxed);
+    if (cus == 0) {
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            cus <= 0)
+            cus = 256;
+        known[dev].store(cus, std::memory_order_relaxed);
+    }
+    return cus;
+}
+
+std::vector<int32_t> strip_launch_order(StepPlan *p, const std::vector<int32_t> &strips_of) {
+    p->strips_ahead = strips_ahead(p->strips, p->n_envs, device_cus());
+    const int first = p->strips_ahead ? 1 : 0;
+    std::vector<int32_t> env;
+    for (int e = 0; e < p->strips_ahead; ++e) env.push_back(e);
+    for (int e = 0; e < p->n_envs; ++e) env.insert(env.end(), strips_of[e] - first, e);
+    return env;
+}
+
 void plan_strip_launch(StepPlan *p, const DevEnv *envs, int n_envs) {
     int cells = 1;
     for (int e = 0; e < n_envs; ++e) cells = std::max(cells, envs[e].strip_cols * envs[e].ncy);
@@ -2006,9 +2033,9 @@ void plan_strip_launch(StepPlan *p, const DevEnv *envs, int n_envs) {
 }
 
 int64_t assign_strips(DevEnv *const *tabs, int n_tabs, int n_envs, int64_t G,
-                      std::vector<int32_t> *strip_env) {
+                      std::vector<int32_t> *strips_of) {
     int64_t S = 0;
-    if (strip_env) strip_env->clear();
+    if (strips_of) strips_of->clear();
     for (int e = 0; e < n_envs; ++e) {
         const int cols = strip_cols_for(tabs[0][e], G);
         const int ns = (tabs[0][e].ncx + cols - 1) / cols;
@@ -2017,7 +2044,7 @@ int64_t assign_strips(DevEnv *const *tabs, int n_tabs, int n_envs, int64_t G,
             tabs[k][e].strip_cols = cols;
             tabs[k][e].n_strips = ns;
         }
-        if (strip_env) strip_env->insert(strip_env->end(), ns, e);
+        if (strips_of) strips_of->push_back(ns);
         S += ns;
     }
     return S;
@@ -2109,18 +2136,18 @@ hipError_t launch_phase(const StepPlan &p, int table, StepPhase phase, int do_mo
     switch (phase) {
         case kPhaseMove:
             if (p.env_sort_recs == 0 && p.strips > 0 && p.strip_now) {
-                const int per_xcd = (int)((p.strips + kXcds - 1) / kXcds);
-                auto go = [&](auto nt, auto r, auto waves) {
-                    constexpr int NT = decltype(nt)::value, R = decltype(r)::value;
-                    hipLaunchKernelGGL((k_strip_sort<NT, R, decltype(waves)::value>), dim3((unsigned)(per_xcd * kXcds)),
-                                       dim3(NT), (size_t)p.strip_cells * sizeof(int), s, p.a, envs,
-                                       p.n_envs, C, G, (int)p.strips, do_move,
+                auto go = [&](auto kernel, int nt) {
+                    hipLaunchKernelGGL(kernel, dim3(strip_blocks(p.strips, p.strips_ahead)), dim3(nt),
+                                       (size_t)p.strip_cells * sizeof(int), s, p.a, envs, p.n_envs,
+                                       C, G, (int)p.strips, do_move,
                                        reinterpret_cast<const float2 *>(act), p.tag,
-                                       reinterpret_cast<float2 *>(act_copy), per_xcd, p.strip_wait);
+                                       reinterpret_cast<float2 *>(act_copy),
+                                       (int)strip_run(p.strips, p.strips_ahead), p.strip_wait);
                 };
                 // one block per CU: latency; more: see the kernel
-                if (p.strips <= 256) go(std::integral_constant<int, 1024>{}, std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
-                else go(std::integral_constant<int, 512>{}, std::integral_constant<int, 3>{}, std::integral_constant<int, 8>{});
+                if (p.strips_ahead > 0) go(k_strip_sort<512, 3, 8, true>, 512);
+                else if (p.strips <= 256) go(k_strip_sort<1024, 4, 4, false>, 1024);
+                else go(k_strip_sort<512, 3, 8, false>, 512);
                 break;
             }
             if (p.env_sort_recs > 0) {

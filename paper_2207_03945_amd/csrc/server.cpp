@@ -317,17 +317,18 @@ int rebuild_plan(srv_t *S) {
     // strips of the running envs (the strip sort), when every env allows it
     bool strips_ok = true;
     for (const DevEnv &d : S->tab[0]) strips_ok = strips_ok && strips_allowed(d);
-    std::vector<int32_t> strip_env;
+    std::vector<int32_t> strips_of, strip_env;
     int64_t n_strips = 0;
     if (strips_ok && !S->tab[0].empty()) {
         DevEnv *tabs[2] = {S->tab[0].data(), S->tab[1].data()};
-        n_strips = assign_strips(tabs, 2, (int)S->running.size(), g, &strip_env);
+        n_strips = assign_strips(tabs, 2, (int)S->running.size(), g, &strips_of);
     }
     Carver cv{S->arena + S->scratch.off, 0};
     carve_sort(cv, g, c, (int)S->running.size(), &S->plan.a, n_strips);
     S->plan.strips = (int)n_strips;
     if (n_strips > 0) plan_strip_launch(&S->plan, S->tab[0].data(), (int)S->running.size());
     S->plan.n_envs = (int)S->running.size();
+    if (n_strips > 0) strip_env = strip_launch_order(&S->plan, strips_of);
     S->plan.G = g;
     S->plan.C = c;
     S->plan.v = S->running.empty() ? 1 : S->reqs.at(S->running[0]).p.sectors;

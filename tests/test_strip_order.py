@@ -1,0 +1,69 @@
+"""Launch order of the strip sort's blocks (csrc/strip_order.h), on the CPU.
+
+Every strip is taken by one block, whatever the device; where a launch's blocks
+are not all resident at once, each env's first strip is taken by a block below
+all that wait for its word; a launch never has more than seven idle blocks.
+The header is plain C++: a small program prints what each block takes.
+"""
+from __future__ import annotations
+
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2207_03945_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <vector>
+#include "strip_order.h"
+int main(int argc, char **argv) {
+    std::vector<int> ns, base, env;   // strips, strips before each env; env of each place
+    int cus = 0, S = 0;
+    if (std::scanf("%d", &cus) != 1) return 1;
+    for (int n; std::scanf("%d", &n) == 1; S += n) ns.push_back(n), base.push_back(S);
+    const int E = (int)ns.size(), ahead = flock::strips_ahead(S, E, cus);
+    for (int e = 0; e < ahead; ++e) env.push_back(e);
+    for (int e = 0; e < E; ++e) env.insert(env.end(), ns[e] - (ahead ? 1 : 0), e);
+    for (unsigned b = 0; b < flock::strip_blocks(S, ahead); ++b) {
+        const int p = flock::strip_place(b, ahead, flock::strip_run(S, ahead));
+        if (p >= S) std::printf("-1 -1\n");
+        else std::printf("%d %d\n", env[p], flock::strip_in_env(p, ahead, env[p], base[env[p]]));
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("strip_order")
+    (d / "main.cpp").write_text(PROGRAM)
+    exe = str(d / "main")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", f"-I{CSRC}", str(d / "main.cpp"), "-o", exe],
+                   check=True)
+    return exe
+
+
+CASES = {
+    "one strip": [1], "one env": [707], "ones": [1] * 300, "four large": [999] * 4,
+    "twenty": [106] * 20, "first alone": [1, 2000], "last alone": [2000, 1],
+    "uneven": [int(k) for k in np.random.default_rng(1).integers(1, 60, 256)],
+}
+
+
+@pytest.mark.parametrize("cus", [32, 256])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_first_strips_come_before_their_waiters(program, name, cus):
+    ns = CASES[name]
+    out = subprocess.run([program], input=" ".join(map(str, [cus] + ns)), text=True, check=True,
+                         capture_output=True).stdout
+    taken = [tuple(map(int, line.split())) for line in out.splitlines()]
+    block = {t: b for b, t in enumerate(taken) if t != (-1, -1)}
+    assert len(taken) - len(block) < 8
+    assert sorted(block) == [(e, k) for e, n in enumerate(ns) for k in range(n)]
+    if len(taken) > 4 * cus:        # four blocks of the sort on a compute unit
+        for (e, k), b in block.items():
+            assert k == 0 or b > block[e, 0], f"strip {k} of env {e} starts before its first"
