@@ -123,6 +123,8 @@ struct StepPlan {
     int strips_ahead = 0;   // envs' first strips at the head of the launch (strip_order.h)
     int strip_now;          // this launch may use the strip sort (every env's records sorted)
     int strip_cells;        // cells of the plan's largest strip
+    int strip_cap = 0;      // agents that a strip block lists in LDS (0: no list)
+    int strips_per_cu = 4;  // strip blocks that a CU holds (by the list's size)
     // polls a strip makes for the edge crossings that its env's first strip
     // counts; when they run out it counts the agents before it itself (0: always)
     int strip_wait = kStripWait;
@@ -191,7 +193,7 @@ int64_t assign_strips(DevEnv *const *tabs, int n_tabs, int n_envs, int64_t G,
 // Choose the plan's launch order of its strips (strip_order.h) for the current
 // device; returns the env of each strip in that order, the plan's strip_env.
 std::vector<int32_t> strip_launch_order(StepPlan *p, const std::vector<int32_t> &strips_of);
-// Fill the plan's strip_cells from its envs' descriptors (after assign_strips).
+// Fill the plan's strip_cells and strip_cap from its envs' descriptors (after assign_strips).
 void plan_strip_launch(StepPlan *p, const DevEnv *envs, int n_envs);
 
 // Launchers (return hipSuccess or the first error) ------------------------

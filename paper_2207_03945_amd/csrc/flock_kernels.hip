@@ -620,8 +620,10 @@ __global__ __launch_bounds__(kEnvNT) void k_env_sort(SortArrays a, const DevEnv 
 // were, before the move, in its columns or in the one on either side.  The
 // block loads and moves those, ranks its agents by cell in LDS, and writes
 // them in cell order with the strip's cell starts.  The first NT * R records
-// stay in registers between counting and placing; a denser strip reads the
-// rest twice (the second time from cache).
+// stay in registers between counting and placing; of the rest, the strip's
+// agents wait in a list in LDS (kList, whose registers take the own columns
+// first; the list sized for uniform agents), and a strip that exceeds it reads
+// the rest twice, actions included.
 //
 // Where the strip's agents go: the agents now in columns below c0 are the
 // records before the block's range, plus those in its range that are now
@@ -645,6 +647,15 @@ __global__ __launch_bounds__(kEnvNT) void k_env_sort(SortArrays a, const DevEnv 
 // clustered envs of 50,000 57.8 -> 42.2 (the densest strip: 5,800 of its 7,000
 // records), 16,000 agents in 20 strips 13.2 -> 11.0, 5,000 in 10 strips
 // 9.6 -> 7.7.
+// In envs of millions a strip is one column of thousands of agents.  One round of
+// probes leaves each end of its range open by n / 256 records, and reading the
+// rest twice gathers every action up to six times: one env of 2 million 297 us,
+// with ends searched to 512 records 212 (to 128 or 1,024 the same), with the
+// list 138 (look-back, tickets and a list of all: 160); four of 4 million 3,800,
+// 1,930 and 1,220 (2,050); one of 300,000 34, 28 and 26 (27).
+constexpr int kStripNear = 512;          // records to which an end of the range is searched
+constexpr int kStripRegs = 512 * 3;      // records in the registers of a block of 512 threads
+constexpr int kStripLds = 156 * 1024;    // LDS of a CU's blocks (160 KiB, less the static part)
 constexpr uint32_t kStripSet = 1u << 31;  // status word: the env's edge crossings are set
 // The wait for that word is bounded (the plan's strip_wait polls).  The first
 // strips run at once with the strips that wait for them or come before them in
@@ -675,13 +686,14 @@ __device__ int strip_base_by_count(const DevEnv &E, int c0, int do_move,
     return cnt;
 }
 
-template <int NT, int R, int kWaves, bool kAhead>
+template <int NT, int R, int kWaves, bool kAhead, bool kList>
 __global__ __launch_bounds__(NT, kWaves) void k_strip_sort(
     SortArrays a, const DevEnv *__restrict__ envs, int n_envs, int C, int G, int S, int do_move,
-    const float2 *__restrict__ act, int tag, float2 *__restrict__ act_copy, int run_len, int wait) {
-    extern __shared__ int s_cells[];  // the strip's cells: counts, then each cell's first row
+    const float2 *__restrict__ act, int tag, float2 *__restrict__ act_copy, int run_len, int wait, int cap) {
+    // the strip's cells: counts, then each cell's first row; then the list
+    extern __shared__ int s_cells[];
     __shared__ int s_wave[NT / 64 + 1], s_probe[NT / 64];
-    __shared__ int s_base, s_side;
+    __shared__ int s_base, s_side, s_listed;
     const int tid = threadIdx.x, lane = tid & 63;
     const int ahead = kAhead ? n_envs : 0;
     const int place = strip_place(blockIdx.x, ahead, run_len);
@@ -693,33 +705,53 @@ __global__ __launch_bounds__(NT, kWaves) void k_strip_sort(
     const int c0 = ls * E.strip_cols, c1 = ls == nst - 1 ? ncx : c0 + E.strip_cols;
     const int cbase = c0 * ncy, ncell = (c1 - c0) * ncy;
     for (int c = tid; c < ncell; c += NT) s_cells[c] = 0;
-    if (tid == 0) s_side = 0;
+    if (tid == 0) s_side = s_listed = 0;
+    int *const s_li = s_cells + ((ncell + 3) & ~3), *const s_lc = s_li + cap;
+    float2 *const s_la = reinterpret_cast<float2 *>(s_lc + cap);
     // A range of old records that holds those of columns c0 - 1 .. c1
     // (periodic; two ranges where they wrap; all records when they cover the
     // box).  Half the block's waves look for either end, one probe per lane
     // at equal distances: columns are nondecreasing, so the probes below a
-    // column are the first ones, and the end is known to n / (NT / 2)
-    // records.  The few records too many fall to the column test below.
+    // column are the first ones, and the end lies between the last of them and
+    // the next.  More rounds probe between the two while they are more than
+    // kStripNear records apart.  The few records too many fall to the column
+    // test below.
     int r0 = 0, r1 = n, r2 = 0;  // [r0, r1) and then [0, r2)
     const bool part = nst > 1 && c1 - c0 + 2 < ncx;
     if (part) {
         constexpr int P = NT / 2;
-        const int step = (n + P - 1) / P, half = tid / P, q = (tid - half * P) * step;
+        const int half = tid / P, q = tid - half * P;
         // first column of the range, first column past it
         const int col = half == 0 ? (c0 == 0 ? ncx : c0) - 1 : (c1 == ncx ? 0 : c1) + 1;
-        const bool lower = q < n && cell_of(gload(E.rec_cur, q).x, E.inv_cx, ncx) < col;
-        const uint64_t m = __ballot(lower);
-        if (lane == 0) s_probe[tid >> 6] = __popcll(m);
-        __syncthreads();
-        int k0 = 0, k1 = 0;
+        // the probes below an end, `step` records apart from lo0 / lo1 on
+        int k0, k1;
+        auto probe = [&](int at) {
+            const bool lower = at < n && cell_of(gload(E.rec_cur, at).x, E.inv_cx, ncx) < col;
+            const uint64_t m = __ballot(lower);
+            if (lane == 0) s_probe[tid >> 6] = __popcll(m);
+            __syncthreads();
+            k0 = k1 = 0;
 #pragma unroll
-        for (int w = 0; w < NT / 128; ++w) {
-            k0 += s_probe[w];
-            k1 += s_probe[NT / 128 + w];
+            for (int w = 0; w < NT / 128; ++w) {
+                k0 += s_probe[w];
+                k1 += s_probe[NT / 128 + w];
+            }
+            k0 = __builtin_amdgcn_readfirstlane(k0);
+            k1 = __builtin_amdgcn_readfirstlane(k1);
+        };
+        int step = (n + P - 1) / P;
+        probe(q * step);
+        int lo = k0 > 0 ? (k0 - 1) * step + 1 : 0, hi = min(k1 * step, n);
+        int lo1 = k1 > 0 ? (k1 - 1) * step + 1 : 0;
+        while (__builtin_expect(step > kStripNear, 0)) {
+            const int width = step;
+            step = (width + P - 1) / P;
+            __syncthreads();  // the last counts are read before the next
+            probe(q * step < width ? (half == 0 ? lo : lo1) + q * step : n);
+            lo += k0 > 0 ? (k0 - 1) * step + 1 : 0;
+            hi = min(lo1 + k1 * step, n);
+            lo1 += k1 > 0 ? (k1 - 1) * step + 1 : 0;
         }
-        k0 = __builtin_amdgcn_readfirstlane(k0);
-        k1 = __builtin_amdgcn_readfirstlane(k1);
-        const int lo = k0 > 0 ? (k0 - 1) * step + 1 : 0, hi = min(k1 * step, n);
         if (c0 == 0 || c1 == ncx) {
             if (lo > hi) r0 = lo, r2 = hi;  // else they meet: all records
         } else {
@@ -730,7 +762,12 @@ __global__ __launch_bounds__(NT, kWaves) void k_strip_sort(
         __syncthreads();
     }
     const int len = r1 - r0, total_old = len + r2;
-    auto index = [&](int v) { return v < len ? r0 + v : v - len; };
+    // the own columns' records first (about: the range's columns counted as equal)
+    const int turn = kList && part ? total_old / (c1 - c0 + 2) : 0;
+    auto index = [&](int v) {
+        const int w = !kList ? v : v + turn < total_old ? v + turn : v + turn - total_old;
+        return w < len ? r0 + w : w - len;
+    };
     // the wave's count of records now below c0, edge crossings taken back; of
     // the crossings, in minus out, in the first strip
     int side = 0;
@@ -803,12 +840,25 @@ __global__ __launch_bounds__(NT, kWaves) void k_strip_sort(
         float2 av[R];
         load_move(v0, id2, m2, av, cell2, std::true_type{});
 #pragma unroll
-        for (int u = 0; u < R; ++u)
+        for (int u = 0; u < R; ++u) {
+            int at = 0;
+            if constexpr (kList) {
+                const uint64_t own = __ballot(cell2[u] >= 0);
+                if (own == 0) continue;
+                if (lane == 0) at = atomicAdd(&s_listed, __popcll(own));
+                at = __builtin_amdgcn_readfirstlane(at) + __popcll(own & ((1ull << lane) - 1ull));
+            }
             if (cell2[u] >= 0) {
                 atomicAdd(&s_cells[cell2[u]], 1);
+                if (kList && at < cap) {
+                    s_li[at] = index(v0 + u * NT);
+                    s_lc[at] = cell2[u];
+                    s_la[at] = av[u];
+                }
                 if (do_move && act_copy && (unsigned)id2[u] < (unsigned)n)
                     act_copy[E.agent_base + id2[u]] = av[u];
             }
+        }
     }
     if (lane == 0 && side != 0) atomicAdd(&s_side, side);
     __syncthreads();
@@ -872,6 +922,28 @@ __global__ __launch_bounds__(NT, kWaves) void k_strip_sort(
 #pragma unroll
     for (int u = 0; u < R; ++u)
         if (cell[u] >= 0) put(base + atomicAdd(&s_cells[cell[u]], 1), m[u], id[u], ret[u]);
+    const int listed = s_listed;
+    if (kList && listed <= cap) {
+        for (int k0 = tid; k0 < listed; k0 += NT * R) {
+            int at[R];
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const int k = min(k0 + u * NT, listed - 1);
+                at[u] = s_li[k];
+                id[u] = gload(E.id_cur, at[u]);
+                m[u] = gload(E.rec_cur, at[u]);
+                ret[u] = gload(E.ret_cur, at[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const int k = k0 + u * NT;
+                if (k >= listed) continue;
+                const float4 r = do_move ? move_record(E, m[u], s_la[k]) : m[u];
+                put(base + atomicAdd(&s_cells[s_lc[k]], 1), r, id[u], ret[u]);
+            }
+        }
+        return;
+    }
     for (int v0 = NT * R + tid; v0 < total_old; v0 += NT * R) {
         float2 av[R];
         load_move(v0, id, m, av, cell, std::false_type{});
@@ -2018,7 +2090,7 @@ static int device_cus() {
 }
 
 std::vector<int32_t> strip_launch_order(StepPlan *p, const std::vector<int32_t> &strips_of) {
-    p->strips_ahead = strips_ahead(p->strips, p->n_envs, device_cus());
+    p->strips_ahead = strips_ahead(p->strips, p->n_envs, p->strips_per_cu * device_cus());
     const int first = p->strips_ahead ? 1 : 0;
     std::vector<int32_t> env;
     for (int e = 0; e < p->strips_ahead; ++e) env.push_back(e);
@@ -2030,6 +2102,28 @@ void plan_strip_launch(StepPlan *p, const DevEnv *envs, int n_envs) {
     int cells = 1;
     for (int e = 0; e < n_envs; ++e) cells = std::max(cells, envs[e].strip_cols * envs[e].ncy);
     p->strip_cells = cells;
+    // Strips whose neighbouring columns alone exceed the registers list their
+    // agents beyond them (uniform agents' and four deviations), in the LDS that
+    // leaves a CU four, three or two blocks.  Where less is read again, reading it
+    // again is as fast (256 uneven envs, half the own agents' number: steps 2 %
+    // slower with a list).
+    p->strip_cap = 0;
+    double list = 0.0;
+    for (int e = 0; e < n_envs; ++e) {
+        const DevEnv &d = envs[e];
+        const double per_col = (double)d.n / d.ncx, own = per_col * d.strip_cols;
+        if (2.0 * per_col <= kStripRegs) continue;
+        const double in = 0.64 * d.s_max / d.cw * per_col;  // come in over either border
+        list = std::max(list, std::max(own - kStripRegs, 0.0) + in + 4.0 * std::sqrt(own));
+    }
+    p->strips_per_cu = 4;
+    for (int k = 4; k >= 2 && list > 0.0 && p->strip_cap == 0; --k) {
+        const int cap = (kStripLds / k / (int)sizeof(int) - ((cells + 3) & ~3)) / 4;
+        if (list <= cap) {
+            p->strip_cap = cap;
+            p->strips_per_cu = k;
+        }
+    }
 }
 
 int64_t assign_strips(DevEnv *const *tabs, int n_tabs, int n_envs, int64_t G,
@@ -2136,18 +2230,22 @@ hipError_t launch_phase(const StepPlan &p, int table, StepPhase phase, int do_mo
     switch (phase) {
         case kPhaseMove:
             if (p.env_sort_recs == 0 && p.strips > 0 && p.strip_now) {
-                auto go = [&](auto kernel, int nt) {
+                auto go = [&](auto kernel, int nt, int cap) {
+                    const size_t lds = (((p.strip_cells + 3) & ~3) + 4 * (size_t)cap) * sizeof(int);
                     hipLaunchKernelGGL(kernel, dim3(strip_blocks(p.strips, p.strips_ahead)), dim3(nt),
-                                       (size_t)p.strip_cells * sizeof(int), s, p.a, envs, p.n_envs,
-                                       C, G, (int)p.strips, do_move,
+                                       lds, s, p.a, envs, p.n_envs, C, G, (int)p.strips, do_move,
                                        reinterpret_cast<const float2 *>(act), p.tag,
                                        reinterpret_cast<float2 *>(act_copy),
-                                       (int)strip_run(p.strips, p.strips_ahead), p.strip_wait);
+                                       (int)strip_run(p.strips, p.strips_ahead), p.strip_wait, cap);
                 };
                 // one block per CU: latency; more: see the kernel
-                if (p.strips_ahead > 0) go(k_strip_sort<512, 3, 8, true>, 512);
-                else if (p.strips <= 256) go(k_strip_sort<1024, 4, 4, false>, 1024);
-                else go(k_strip_sort<512, 3, 8, false>, 512);
+                const bool ahead = p.strips_ahead > 0;
+                const int cap = p.strip_cap;
+                if (!ahead && p.strips <= 256) go(k_strip_sort<1024, 4, 4, false, false>, 1024, 0);
+                else if (ahead && cap) go(k_strip_sort<512, 3, 8, true, true>, 512, cap);
+                else if (ahead) go(k_strip_sort<512, 3, 8, true, false>, 512, 0);
+                else if (cap) go(k_strip_sort<512, 3, 8, false, true>, 512, cap);
+                else go(k_strip_sort<512, 3, 8, false, false>, 512, 0);
                 break;
             }
             if (p.env_sort_recs > 0) {

@@ -18,12 +18,10 @@ namespace flock {
 
 constexpr int kXcds = 8;  // MI355X: accelerator dies (XCDs), each with its own L2
 
-// Blocks of up to 64 registers a lane and 32 KiB of cells that a CU holds.
-constexpr int kStripsPerCu = 4;
-
-// First strips at the launch's head: all n_envs of them or none.
-constexpr int strips_ahead(int S, int n_envs, int cus) {
-    return n_envs > 1 && S + kXcds > kStripsPerCu * cus ? n_envs : 0;
+// First strips at the launch's head: all n_envs of them, or none where all
+// blocks are among the `resident` ones that the device holds at once.
+constexpr int strips_ahead(int S, int n_envs, int resident) {
+    return n_envs > 1 && S + kXcds > resident ? n_envs : 0;
 }
 
 // Strips of one XCD's run.
