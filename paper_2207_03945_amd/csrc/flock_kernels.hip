@@ -2241,7 +2241,7 @@ hipError_t launch_phase(const StepPlan &p, int table, StepPhase phase, int do_mo
                 // one block per CU: latency; more: see the kernel
                 const bool ahead = p.strips_ahead > 0;
                 const int cap = p.strip_cap;
-                if (!ahead && p.strips <= 256) go(k_strip_sort<1024, 4, 4, false, false>, 1024, 0);
+                if (!ahead && strips_wide(p.strips, device_cus())) go(k_strip_sort<1024, 4, 4, false, false>, 1024, 0);
                 else if (ahead && cap) go(k_strip_sort<512, 3, 8, true, true>, 512, cap);
                 else if (ahead) go(k_strip_sort<512, 3, 8, true, false>, 512, 0);
                 else if (cap) go(k_strip_sort<512, 3, 8, false, true>, 512, cap);

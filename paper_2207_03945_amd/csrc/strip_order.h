@@ -18,6 +18,11 @@ namespace flock {
 
 constexpr int kXcds = 8;  // MI355X: accelerator dies (XCDs), each with its own L2
 
+// Whether a launch takes blocks of 1,024 threads: while a CU of the device has at
+// most one block, its latency counts (10,000 agents in 9 strips: 3 us less than
+// with 512 threads), and fewer CUs would take several rounds of such blocks.
+constexpr bool strips_wide(int S, int cus) { return S <= cus; }
+
 // First strips at the launch's head: all n_envs of them, or none where all
 // blocks are among the `resident` ones that the device holds at once.
 constexpr int strips_ahead(int S, int n_envs, int resident) {

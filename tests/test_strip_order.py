@@ -21,6 +21,8 @@ PROGRAM = r"""
 #include <vector>
 #include "strip_order.h"
 int main(int argc, char **argv) {
+    static_assert(flock::strips_wide(256, 256) && !flock::strips_wide(257, 256), "");
+    static_assert(flock::strips_wide(32, 32) && !flock::strips_wide(200, 32), "a partition's CUs");
     std::vector<int> ns, base, env;   // strips, strips before each env; env of each place
     int resident = 0, S = 0;
     if (std::scanf("%d", &resident) != 1) return 1;
