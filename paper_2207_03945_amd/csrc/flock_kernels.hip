@@ -1336,11 +1336,12 @@ __device__ __forceinline__ int add_bit(int n, uint64_t b) {
     return r;
 }
 
-// The candidates of the wave's agents in env E: neighbours per lane into nb
-// (tag: runners), minima and collision counts in LDS.  mine: the lane's agent
-// exists and lives in E; every lane of the wave takes part.  smin_w: minima of
-// the wave's first agent (agent i's i words on).
-template <int A, int G, bool kFov, bool kTag, int kM>
+// The candidates of the wave's agents: neighbours per lane into nb (tag:
+// runners), minima and collision counts in LDS.  mine: the lane's agent exists;
+// every lane of the wave takes part.  smin_w: minima of the wave's first agent
+// (agent i's i words on).  E is the env of all of them, or, with kMixed, that of
+// the lane's own agent: then every value of it differs from lane to lane.
+template <int A, int G, bool kFov, bool kTag, int kM, bool kMixed>
 __device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E, uint32_t *smin_w,
                                             const WaveQueue &Q, bool mine, float4 me, int pos,
                                             int ti, const ViewK &K, int &nb, int &col) {
@@ -1354,24 +1355,34 @@ __device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E
     auto drain = [&](int n) {
         cnt -= n;
         wave_lds_fence();
+        int o = 0, meta = 0;
+        if constexpr (G < 64 || kTag) {
+            if (lane < n) meta = (int)Q.meta[cnt + lane];
+            o = kTag ? meta & 63 : meta;
+        }
+        // what the entry's agent's env says of it
+        float oc2 = c2, ohalf = K.fov_half, ot = K.fov_t, oscale = K.sec_scale;
+        if constexpr (kMixed) {
+            oc2 = __shfl(c2, o * G, 64);
+            if constexpr (kFov) {
+                ohalf = __shfl(K.fov_half, o * G, 64);
+                ot = __shfl(K.fov_t, o * G, 64);
+                oscale = __shfl(K.sec_scale, o * G, 64);
+            }
+        }
         if (lane < n) {
             const float2 d = make_float2(Q.x[cnt + lane], Q.y[cnt + lane]);
-            int o = 0, meta = 0;
-            if constexpr (G < 64 || kTag) {
-                meta = (int)Q.meta[cnt + lane];
-                o = kTag ? meta & 63 : meta;
-            }
             const float2 cs = G < 64 ? Q.cs[o] : make_float2(K.c, K.s);
             const float d2 = __builtin_fmaf(d.x, d.x, d.y * d.y);
             int ch = 0;
             if constexpr (kTag) ch = (meta & 64) ? K.v : 0;
             int k;
             if constexpr (kFov)
-                k = view_sector(d.x, d.y, cs.x, cs.y, K.fov_half, K.fov_t, K.sec_scale, K.v);
+                k = view_sector(d.x, d.y, cs.x, cs.y, ohalf, ot, oscale, K.v);
             else if constexpr (kM > 0) k = sector_oct<kM>(d.x, d.y, cs.x, cs.y);
             else k = sector_of(d.x, d.y, cs.x, cs.y, K.vf, K.v);
             if (!kFov || k >= 0) atomicMin(&smin_w[(ch + k) * A + o], __float_as_uint(d2));
-            if (d2 < c2 && (!kTag || (meta & 128))) atomicAdd(&Q.col[o], 1);
+            if (d2 < oc2 && (!kTag || (meta & 128))) atomicAdd(&Q.col[o], 1);
         }
         wave_lds_fence();
     };
@@ -1450,13 +1461,14 @@ __device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E
     using Shift = std::integral_constant<int, 1>;
     using Image = std::integral_constant<int, 2>;
 
-    if (ncx == 1) {
-        run(Image{}, Yes{}, a.start[cb], mine ? a.start[cb + 1] - a.start[cb] : 0, 0.0f, 0.0f, 0.0f, 0.0f);
-    } else {
+    const bool single = mine && ncx == 1;
+    if (kMixed ? __any(single) : ncx == 1)
+        run(Image{}, Yes{}, a.start[cb], single ? a.start[cb + 1] - a.start[cb] : 0, 0.0f, 0.0f, 0.0f, 0.0f);
+    if (kMixed ? __any(mine && ncx > 1) : ncx > 1) {
         const int cx = cell_of(me.x, E.inv_cx, ncx);
         const float fx = me.x - (float)cx * E.cw;  // offset within the own column
         const RowGeom RG{E.cw, E.marg, r2, E.inv_cy, ncy};
-        const int nc = 2 * reach + 1;
+        const int nc = kMixed && __any(mine && reach == 2) ? 5 : 2 * (kMixed ? 1 : reach) + 1;
         // lane li plans column li (four lanes: and column 4 + li): run A, its
         // rows inside the column, and run B, those that wrap through the
         // column's ends (as [q, q + l) in cell order)
@@ -1464,7 +1476,7 @@ __device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E
         int qa[kSets], la[kSets], qb[kSets], lb[kSets];
 #pragma unroll
         for (int r = 0; r < kSets; ++r) {
-            const int c = min(li + r * G, nc - 1), ox = c - reach;
+            const int c = min(li + r * G, 2 * reach), ox = c - reach;
             int lo = 0, hi = -1;
             const bool any = column_rows(RG, fx, ox, me.y, lo, hi);
             int ccx = cx + ox;
@@ -1479,7 +1491,7 @@ __device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E
                 qb[r] = a.start[colb + j0];
                 lb[r] = a.start[colb + j1] - qb[r];
             }
-            if (!mine || !any) la[r] = lb[r] = 0;
+            if (!mine || !any || (kMixed && (ncx == 1 || c < li + r * G))) la[r] = lb[r] = 0;
         }
         const bool wraps = __any(lb[0] > 0 || lb[kSets - 1] > 0);
         // a column left of column 0 wraps to the right edge with its candidates
@@ -1497,7 +1509,7 @@ __device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E
             const int ccx = cx + c - reach;
             const float offx = ccx < 0 ? -L : 0.0f, xi = ccx >= ncx ? me.x - L : me.x;
             const int q = of(qa), l = of(la);
-            if (__any(ccx < 0 || ccx >= ncx)) run(Shift{}, Yes{}, q, l, offx, xi, 0.0f, me.y);
+            if (kMixed || __any(ccx < 0 || ccx >= ncx)) run(Shift{}, Yes{}, q, l, offx, xi, 0.0f, me.y);
             else if (c == reach) run(Plain{}, Yes{}, q, l, 0.0f, 0.0f, 0.0f, 0.0f);
             else run(Plain{}, No{}, q, l, 0.0f, 0.0f, 0.0f, 0.0f);
             if (wraps) {
@@ -1643,19 +1655,19 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
             Q.cs[lane / G] = cs;
             Q.col[lane / G] = 0;
         }
-        // env by env (few waves hold agents of more than one), so that the
-        // descriptor is wave-uniform: scalar loads and registers
-        for (uint64_t todo = __ballot(active); todo != 0;) {
-            const int e0 = __builtin_amdgcn_readlane(e, __builtin_ctzll(todo));
-            const bool mine = active && e == e0;
-            todo &= ~__ballot(mine);
+        const ViewK K{cs.x, cs.y, E.fov_half, E.fov_t, E.sec_scale, (float)v, v};
+        if (kTag && active) ti = my_id < E.n_chasers ? 1 : 0;
+        uint32_t *const smin_w = s_min + (tid >> 6) * (64 / G);
+        const int e0 = __builtin_amdgcn_readfirstlane(e);
+        if (G == 64 || !__any(active && e != e0)) {
+            // one env, as in nearly every wave: its descriptor in scalar registers
             int eu = e0;
             asm("" : "+s"(eu));  // (else the compiler takes the lane's own equal e)
             const DevEnv &U = envs[eu];
-            const ViewK K{cs.x, cs.y, U.fov_half, U.fov_t, U.sec_scale, (float)v, v};
-            if (kTag && mine) ti = my_id < U.n_chasers ? 1 : 0;
-            sweep_group<A, G, kFov, kTag, kM>(a, U, s_min + (tid >> 6) * (64 / G), Q, mine, me, pos,
-                                              ti, K, nb, col);
+            const ViewK KU{cs.x, cs.y, U.fov_half, U.fov_t, U.sec_scale, (float)v, v};
+            sweep_group<A, G, kFov, kTag, kM, false>(a, U, smin_w, Q, active, me, pos, ti, KU, nb, col);
+        } else if constexpr (G < 64) {
+            sweep_group<A, G, kFov, kTag, kM, true>(a, E, smin_w, Q, active, me, pos, ti, K, nb, col);
         }
         if constexpr (queued(G, kM)) {
             col = Q.col[lane / G];
