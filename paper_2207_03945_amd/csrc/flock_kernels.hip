@@ -1297,34 +1297,44 @@ __device__ __forceinline__ void flat_runs(const RowGeom &RG, const int32_t *__re
 // two 36.6 -> 28.9 us).
 constexpr int kQueue = 63 + 64 * kGroupUnroll + 1;  // entries: a rest below 64, one step's pushes
 
-// Whether a lane group's sweep queues its neighbours: views whose sector takes
-// the arctangent, and steps of 64 lanes.  Sectors by octant (kM > 0) cost
+// Whether a lane group's sweep queues its neighbours (meta: bytes per entry
+// beside its displacement, 0 for plans of single cells): views whose sector takes the
+// arctangent, and steps of 64 lanes.  Sectors by octant (kM > 0) cost
 // about what a push and a pop do, so where most candidates are neighbours they
 // are evaluated in place (20 x 50,000 clustered agents at four lanes: 266 us
 // per step against 309 queued, 282 before); with 64 lanes few lanes of a slot
 // have one (one 5,000-agent env: 16.7 us per step against 17.7 in place).
-__host__ __device__ constexpr bool queued(int G, int kM) { return kM == 0 || G == 64; }
-
-// 32-bit words of LDS per wave.
-__host__ __device__ constexpr int queue_words(int G, int kM) {
-    return queued(G, kM) ? (3 * kQueue + 3 * (64 / G) + 3) & ~3 : 0;
+// Single cells, whose boxes are hardly wider than a view, are evaluated in
+// place at four lanes, and at 16 if the view is full (1,000 agents in a box of
+// 20, 20 sectors, four lanes: 79 us per step, 95 queued, with a view of 250
+// degrees 88 and 101; 200 envs of 600 at 16 lanes 98 and 102); plans of nothing
+// else have no queue there.
+__host__ __device__ constexpr bool queued(int G, int kM, int meta) {
+    return meta > 0 && (kM == 0 || G == 64);
 }
 
+// 32-bit words of LDS per wave.
+__host__ __device__ constexpr int queue_words(int G, int kM, int meta) {
+    return queued(G, kM, meta) ? (2 * kQueue + meta * kQueue / 4 + 3 * (64 / G) + 3) & ~3 : 0;
+}
+
+template <int kMeta>
 struct WaveQueue {
-    float *x, *y;    // [kQueue] displacement of a neighbour from its agent
-    uint32_t *meta;  // [kQueue] agent of the entry; tag: + 64 type, + 128 types differ
-    float2 *cs;      // [64 / G] cos / sin of the agents' headings
-    int *col;        // [64 / G] collisions (tag: touches)
+    using Meta = std::conditional_t<kMeta == 1, uint8_t, uint32_t>;
+    float *x, *y;        // [kQueue] displacement of a neighbour from its agent
+    float2 *cs;          // [64 / G] cos / sin of the agents' headings
+    int *col;            // [64 / G] collisions (tag: touches)
+    Meta *meta;          // [kQueue] agent of the entry; tag: + 64 type, + 128 types differ
 };
 
-template <int G>
-__device__ __forceinline__ WaveQueue wave_queue(uint32_t *words) {
-    WaveQueue Q;
+template <int G, int kMeta>
+__device__ __forceinline__ WaveQueue<kMeta> wave_queue(uint32_t *words) {
+    WaveQueue<kMeta> Q;
     Q.x = reinterpret_cast<float *>(words);
     Q.y = Q.x + kQueue;
-    Q.meta = words + 2 * kQueue;
-    Q.cs = reinterpret_cast<float2 *>(words + 3 * kQueue);
+    Q.cs = reinterpret_cast<float2 *>(words + 2 * kQueue);
     Q.col = reinterpret_cast<int *>(Q.cs + 64 / G);
+    Q.meta = reinterpret_cast<typename WaveQueue<kMeta>::Meta *>(Q.col + 64 / G);
     return Q;
 }
 
@@ -1341,14 +1351,15 @@ __device__ __forceinline__ int add_bit(int n, uint64_t b) {
 // every lane of the wave takes part.  smin_w: minima of the wave's first agent
 // (agent i's i words on).  E is the env of all of them, or, with kMixed, that of
 // the lane's own agent: then every value of it differs from lane to lane.
-template <int A, int G, bool kFov, bool kTag, int kM, bool kMixed>
+template <int A, int G, bool kFov, bool kTag, int kM, bool kMixed, int kMeta>
 __device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E, uint32_t *smin_w,
-                                            const WaveQueue &Q, bool mine, float4 me, int pos,
+                                            const WaveQueue<kMeta> &Q, bool mine, float4 me, int pos,
                                             int ti, const ViewK &K, int &nb, int &col) {
     const int lane = threadIdx.x & 63, li = lane % G, own = lane / G;
     const float L = E.box, r2 = E.r2, c2 = E.c2;
     const int ncx = E.ncx, ncy = E.ncy, cb = E.cell_base, reach = E.reach;
-    constexpr bool kQueued = queued(G, kM);
+    constexpr bool kQueued = queued(G, kM, kMeta);
+    using Meta = typename WaveQueue<kMeta>::Meta;
     int cnt = 0;  // queued entries (wave-uniform)
 
     // the last n (at most 64) entries, one per lane
@@ -1392,7 +1403,7 @@ __device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E
     auto run = [&](auto kmode, auto kself, int q, int len, float offx, float xi, float offy,
                    float yi) {
         constexpr int kMode = decltype(kmode)::value;
-        if constexpr (!kQueued) {
+        if constexpr (!kQueued || (kMode == 2 && G <= 16 && !kFov && !kTag)) {
             constexpr int U = G == 4 ? 4 : kGroupUnroll;
             for (int t = li; t < len; t += U * G) {
                 float2 p[U];
@@ -1407,6 +1418,10 @@ __device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E
                         kMode == 1 ? xi : me.x, offy, kMode == 1 ? yi : me.y, kMode == 2, L, r2,
                         c2, K, nb, col);
                 }
+            }
+            if (kQueued && col > 0) {
+                atomicAdd(&Q.col[own], col);
+                col = 0;
             }
             return;
         }
@@ -1447,8 +1462,8 @@ __device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E
                     (Q.x + cnt)[k] = dx;
                     (Q.y + cnt)[k] = dy;
                     if constexpr (kTag)
-                        (Q.meta + cnt)[k] = (uint32_t)(own | (tj[u] ? 64 : 0) | (tj[u] != ti ? 128 : 0));
-                    else if constexpr (G < 64) (Q.meta + cnt)[k] = (uint32_t)own;
+                        (Q.meta + cnt)[k] = (Meta)(own | (tj[u] ? 64 : 0) | (tj[u] != ti ? 128 : 0));
+                    else if constexpr (G < 64) (Q.meta + cnt)[k] = (Meta)own;
                 }
                 cnt += n;
             }
@@ -1464,7 +1479,7 @@ __device__ __forceinline__ void sweep_group(const SortArrays &a, const DevEnv &E
     const bool single = mine && ncx == 1;
     if (kMixed ? __any(single) : ncx == 1)
         run(Image{}, Yes{}, a.start[cb], single ? a.start[cb + 1] - a.start[cb] : 0, 0.0f, 0.0f, 0.0f, 0.0f);
-    if (kMixed ? __any(mine && ncx > 1) : ncx > 1) {
+    if (kMeta > 0 && (kMixed ? __any(mine && ncx > 1) : ncx > 1)) {
         const int cx = cell_of(me.x, E.inv_cx, ncx);
         const float fx = me.x - (float)cx * E.cw;  // offset within the own column
         const RowGeom RG{E.cw, E.marg, r2, E.inv_cy, ncy};
@@ -1586,12 +1601,12 @@ __device__ __forceinline__ int sweep_block(int b, int nb, int log_run) {
 
 // 32-bit words of LDS of a sweep block before the policy's: the minima, then
 // (lane groups) each wave's queue.
-__host__ __device__ constexpr int sweep_words(int vs, int NT, int G, int kM) {
+__host__ __device__ constexpr int sweep_words(int vs, int NT, int G, int kM, int meta) {
     const int minima = vs * (NT / G);
-    return G == 1 ? minima : ((minima + 3) & ~3) + NT / 64 * queue_words(G, kM);
+    return G == 1 ? minima : ((minima + 3) & ~3) + NT / 64 * queue_words(G, kM, meta);
 }
 
-template <int NT, int G, bool kFov, bool kTag, int kM, int kPol = 0>
+template <int NT, int G, bool kFov, bool kTag, int kM, int kPol, int kMeta>
 __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__restrict__ envs,
                                               int n_envs, int Gtot, int v, int obs_dim,
                                               float *__restrict__ obs, float *__restrict__ reward,
@@ -1611,7 +1626,7 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
         for (int k = li; k < vs; k += G) smin[k * A] = kInfBits;
     static_assert(kPol == 0 || G <= 4, "the fused policy needs blocks of at least 64 agents");
     const SweepPolLds PL =
-        sweep_pol_lds(sweep_words(vs, NT, G, kM), A, NT, G, sweep_pol_alias(G, pf.kc, vs));
+        sweep_pol_lds(sweep_words(vs, NT, G, kM, kMeta), A, NT, G, sweep_pol_alias(G, pf.kc, vs));
     PolConsts *s_pc = reinterpret_cast<PolConsts *>(s_min + PL.pc);
     float *s_speed = reinterpret_cast<float *>(s_min + PL.speed);
     int *s_pe = reinterpret_cast<int *>(s_min + PL.env);
@@ -1649,9 +1664,11 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
     }
     if constexpr (G > 1) {
         const int lane = tid & 63;
-        const WaveQueue Q = wave_queue<G>(s_min + ((vs * A + 3) & ~3) + (tid >> 6) * queue_words(G, kM));
+        const WaveQueue<kMeta> Q = wave_queue<G, kMeta>(
+            s_min + ((vs * A + 3) & ~3) + (tid >> 6) * queue_words(G, kM, kMeta));
         const float2 cs = heading_cs(me.z);
-        if (queued(G, kM) && li == 0) {
+        constexpr bool kQueued = queued(G, kM, kMeta);
+        if (kQueued && li == 0) {
             Q.cs[lane / G] = cs;
             Q.col[lane / G] = 0;
         }
@@ -1669,7 +1686,7 @@ __global__ __launch_bounds__(NT) void k_sweep(SortArrays a, const DevEnv *__rest
         } else if constexpr (G < 64) {
             sweep_group<A, G, kFov, kTag, kM, true>(a, E, smin_w, Q, active, me, pos, ti, K, nb, col);
         }
-        if constexpr (queued(G, kM)) {
+        if constexpr (kQueued) {
             col = Q.col[lane / G];
 #pragma unroll  // (64 lanes: nb is the whole group's already)
             for (int m = (G < 64 || kTag) ? G / 2 : 0; m >= 1; m >>= 1) nb += __shfl_xor(nb, m, 64);
@@ -2190,16 +2207,26 @@ hipError_t launch_clear(const StepPlan &p, hipStream_t s) {
 }
 
 namespace {
-template <int NT, int G, bool kFov, bool kTag, int kM = 0, int kPol = 0>
+template <int NT, int G, bool kFov, bool kTag, int kM = 0, int kPol = 0, int kMeta = 4>
 void launch_sweep_v(const StepPlan &p, const DevEnv *envs, int Gtot, float *obs, float *reward,
                     int add_return, hipStream_t s, const PolFuse *pf) {
     constexpr int A = NT / G;
-    const int vs = (kTag ? 2 : 1) * p.v, min_words = sweep_words(vs, NT, G, kM);
+    const int vs = (kTag ? 2 : 1) * p.v, min_words = sweep_words(vs, NT, G, kM, kMeta);
+    if constexpr (G == 4 && kM == 0 && kPol == 0 && kMeta == 4) {
+        // blocks in a CU's 160 KiB (1,280 bytes at a time, 64 of them static) and registers
+        auto blocks = [](int words) {
+            return std::min(8, 163840 / ((4 * words + 64 + 1279) / 1280 * 1280));
+        };
+        auto go = [&](auto launch) { launch(p, envs, Gtot, obs, reward, add_return, s, pf); };
+        if (p.max_env_cells == 1) return go(launch_sweep_v<NT, G, kFov, kTag, kM, kPol, 0>);
+        if (blocks(sweep_words(vs, NT, G, kM, 1)) > blocks(min_words))
+            return go(launch_sweep_v<NT, G, kFov, kTag, kM, kPol, 1>);
+    }
     const size_t lds =
         (size_t)(kPol ? sweep_pol_lds(min_words, A, NT, G, sweep_pol_alias(G, pf->kc, vs)).words
                       : min_words) *
         sizeof(uint32_t);
-    hipLaunchKernelGGL((k_sweep<NT, G, kFov, kTag, kM, kPol>), dim3(blocks_for(Gtot, A)), dim3(NT),
+    hipLaunchKernelGGL((k_sweep<NT, G, kFov, kTag, kM, kPol, kMeta>), dim3(blocks_for(Gtot, A)), dim3(NT),
                        lds, s, p.a, envs, p.n_envs, Gtot, p.v, p.obs_dim, obs, reward, add_return,
                        pf ? *pf : PolFuse{});
 }
