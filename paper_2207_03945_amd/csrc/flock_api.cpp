@@ -251,6 +251,7 @@ int upload_own(env_t *e, hipStream_t s) {
     if (e->uploaded) return ENV_OK;
     const hipError_t err = launch_bind_one(e->plan, e->own[0], e->own[1], e->p.n_agents, s);
     if (err != hipSuccess) return hip_fail(err, "env descriptor upload");
+    plan_strip_device(&e->plan);
     e->uploaded = true;
     return ENV_OK;
 }

@@ -41,7 +41,6 @@
 #include <limits.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 
 #include <type_traits>
@@ -2103,23 +2102,17 @@ int strip_cols_for(const DevEnv &d, int64_t G) {
     return std::min(cols, d.ncx);
 }
 
-// CUs of the current device, read once per device.
-static int device_cus() {
-    static std::atomic<int> known[64];
+void plan_strip_device(StepPlan *p) {
     int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    cus = known[dev].load(std::memory_order_relaxed);
-    if (cus == 0) {
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            cus <= 0)
-            cus = 256;
-        known[dev].store(cus, std::memory_order_relaxed);
-    }
-    return cus;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
+    p->strips_wide = strips_wide(p->strips, cus);
+    p->strips_ahead = strips_ahead(p->strips, p->n_envs, p->strips_per_cu * cus);
 }
 
 std::vector<int32_t> strip_launch_order(StepPlan *p, const std::vector<int32_t> &strips_of) {
-    p->strips_ahead = strips_ahead(p->strips, p->n_envs, p->strips_per_cu * device_cus());
+    plan_strip_device(p);
     const int first = p->strips_ahead ? 1 : 0;
     std::vector<int32_t> env;
     for (int e = 0; e < p->strips_ahead; ++e) env.push_back(e);
@@ -2280,7 +2273,7 @@ hipError_t launch_phase(const StepPlan &p, int table, StepPhase phase, int do_mo
                 // one block per CU: latency; more: see the kernel
                 const bool ahead = p.strips_ahead > 0;
                 const int cap = p.strip_cap;
-                if (!ahead && strips_wide(p.strips, device_cus())) go(k_strip_sort<1024, 4, 4, false, false>, 1024, 0);
+                if (p.strips_wide && !ahead) go(k_strip_sort<1024, 4, 4, false, false>, 1024, 0);
                 else if (ahead && cap) go(k_strip_sort<512, 3, 8, true, true>, 512, cap);
                 else if (ahead) go(k_strip_sort<512, 3, 8, true, false>, 512, 0);
                 else if (cap) go(k_strip_sort<512, 3, 8, false, true>, 512, cap);
