@@ -6,8 +6,8 @@
 // layer, the two outputs scaled to the turn / speed-change ranges of Sec. 4.1.
 //
 // Precision: inputs and weights rounded once to BF16 (round to nearest even),
-// products accumulated in FP32 by v_mfma_f32_16x16x32_bf16, biases and the
-// 64 -> 2 output layer in FP32 on the vector ALUs (with BF16-rounded weights).
+// products accumulated in FP32 by v_mfma_f32_16x16x32_bf16 from the FP32 biases
+// on; each hidden layer's tanh in FP32, rounded to BF16 as the next layer's input.
 //
 // Layout: see policy_tile.h (one wave per 16-agent tile, hidden units as MFMA
 // rows, layer 1 -> layer 2 through a per-wave LDS tile).  Small tiles keep the
@@ -79,14 +79,20 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 // Rows are agents: one wave per 16-row tile, tiles strided over the grid's
 // waves.  Lane (g, col) takes inputs 32 c + 8 g .. + 7 of the tile's row col
 // straight from its row, in two 16-byte loads (rows of any length, so 4-byte
-// aligned) that each chunk issues before the products of the chunk before it,
-// across tiles; the four lane groups read 128 consecutive bytes of each row.
+// aligned); the four lane groups read 128 consecutive bytes of each row.
 // Copying tiles through LDS first took some ten vector instructions per input
-// (1M rows of 16: 62.1 -> 39.7 us; critic over 129 x 16,000 rows of 129 and
-// advantages: 300 -> 260 us, the critic's 241 us reading its views at 4.4 TB/s;
-// a large copy moves 5.2).  Bound: tanh on the vector ALUs for short rows (128
+// (1M rows of 16: 62.1 -> 38.4 us; critic over 129 x 16,000 rows of 129 and
+// advantages: 300 -> 257 us, the critic's 241 us reading its views at 4.4 TB/s;
+// a large copy moves 5.2).  Issuing a chunk's loads before the products of the
+// chunk before it, across tiles, was slower (500,000 rows of 129 52.6 us, now
+// 50.2; 65,536 of 32 7.1, now 6.1), two chunks ahead slower still (54.2): the
+// waves of a CU cover each other's loads.
+// Bound: tanh on the vector ALUs for short rows (128
 // per row, whose exp and reciprocal issue at a quarter of the rate of an FMA:
-// about 27 us of issue per 1M rows), reading the rows for long ones.
+// about 27 us of issue per 1M rows), reading the rows for long ones, one tile's
+// latency for few (so nothing but the layer-1 copy waits before the first tile:
+// the other weights and the draws are loaded beside the rows, 2,000 rows of 256
+// sampled 7.4 -> 6.0 us).
 // Layer 1's A operand lives in LDS, loaded once per block; kReg: the other
 // layers' in registers, else in LDS too.  Layer 1's results reach layer 2's B
 // operand (eight consecutive hidden units per lane group) through a per-wave
@@ -161,33 +167,35 @@ __global__ __launch_bounds__(NT) void k_policy(PolArgs A) {
     };
 
     Row row{};
-    float f[8];
     int64_t tile = find((int64_t)blockIdx.x * (NT / 64) + wid, row);
-    if (tile < tiles) load(row, 0, f);
     for (int i = threadIdx.x; i < kc * 256; i += NT) s_w1[i] = N.P.w1[i];
+    if constexpr (!kReg) {
+        for (int i = threadIdx.x; i < 512; i += NT) s_w2[i] = N.P.w2[i];
+        if (threadIdx.x < 128) s_w3[threadIdx.x] = N.P.w3[threadIdx.x];
+    }
+    load_pol_consts(N.P, &s_pc, threadIdx.x, NT);
+    __syncthreads();
     bf16x8 w2[kReg ? 8 : 1], w3[kReg ? 2 : 1];
     if constexpr (kReg) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) w2[k] = N.P.w2[k * 64 + lane];
 #pragma unroll
         for (int k = 0; k < 2; ++k) w3[k] = N.P.w3[k * 64 + lane];
-    } else {
-        for (int i = threadIdx.x; i < 512; i += NT) s_w2[i] = N.P.w2[i];
-        if (threadIdx.x < 128) s_w3[threadIdx.x] = N.P.w3[threadIdx.x];
     }
-    load_pol_consts(N.P, &s_pc, threadIdx.x, NT);
-    __syncthreads();
 
     while (tile < tiles) {
-        Row next{};
+        const int64_t agent = tile * 16 + col;
+        float2 e = make_float2(0.0f, 0.0f);
+        if (kOut == kSample && g == 0 && row.valid) e = A.eps[agent];
+        Row next{};  // found meanwhile
         const int64_t tnext = find(tile + waves, next);
-        // the tile's inputs as BF16, the next chunk's (or tile's) loads issued
+        // the tile's inputs as BF16
         auto xb = [&](int c) {
             bf16x8 x;
+            float f[8];
+            load(row, c, f);
 #pragma unroll
             for (int j = 0; j < 8; ++j) x[j] = (__bf16)f[j];
-            if (c + 1 < kc) load(row, c + 1, f);
-            else if (tnext < tiles) load(next, 0, f);
             return x;
         };
         auto w1a = [&](int c, int t) { return s_w1[(c * 4 + t) * 64 + lane]; };
@@ -202,11 +210,9 @@ __global__ __launch_bounds__(NT) void k_policy(PolArgs A) {
         auto hrow = [&](int r) { return s_hid + r * kHidLd; };
         const float2 z = mlp_tile(kc, xb, w1a, w2a, w3a, s_pc, hrow, lane);
         if (g == 0 && row.valid) {
-            const int64_t agent = tile * 16 + col;
             if constexpr (kOut == kValue) {
                 A.val[agent] = z.x;
             } else {
-                const float2 e = kOut == kSample ? A.eps[agent] : make_float2(0.0f, 0.0f);
                 *row.act = pol_output<kOut == kSample>(z, N.max_turn, N.max_dspeed, e, N.sig0,
                                                        N.sig1, N.logp_c,
                                                        A.logp ? A.logp + agent : nullptr);
@@ -290,8 +296,13 @@ hipError_t launch_pol(const PolArgs &a, hipStream_t s) {
     // blocks 44.2 us, 1,536 41.3, 2,048 39.7, 4,096 40.1).  Long rows are
     // bound by their reads, and the LDS by layer 1's operands (four waves and
     // registers 261 us, all in LDS 309); small launches by one tile's latency.
+    // The line: 40,000 rows of 16 take 5.5 us in LDS and 5.4 in registers, 65,536
+    // 5.6 and 6.0, 98,304 6.7 and 7.2, 262,144 12.7 and 15.0.
+    // As many blocks of the other form as are resident: four to a CU, three where
+    // layer 1 has eight or nine chunks of 4 KiB (500,000 rows of 256: 1,024 blocks
+    // 131 us, 768 102).
     if (a.kc == 1 && tiles > 4096) go(k_policy<512, false, kOut>, 512, false, 2048);
-    else go(k_policy<256, true, kOut>, 256, true, 1024);
+    else go(k_policy<256, true, kOut>, 256, true, a.kc < 8 ? 1024 : 768);
     return hipGetLastError();
 }
 
