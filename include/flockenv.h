@@ -405,8 +405,8 @@ int env_step_policy(env_batch_t *b, pol_t *pol, float *act, float *obs, float *r
  *   weight   device FP32 [n_edges]
  *   op_in, op_out  device FP32 [n], distinct
  * Updates run in FP64, rounded once to FP32.  lanes: lanes per node (1, 4,
- * 16, 64; 0 = from the mean degree and the number of edges, where short rows
- * may be taken in blocks).  With lanes = 1 each node applies its edges one by
+ * 16, 64; 0 = from the mean degree and the number of edges, where long rows
+ * may be taken by whole waves and short ones in blocks).  With lanes = 1 each node applies its edges one by
  * one in the stated order; otherwise parts of the row may be composed as
  * affine maps (the same map up to FP64 rounding).  0 <= n <
  * 2^31.  ENV_EINVAL on bad sizes, NULL arrays, op_in == op_out. */

@@ -145,10 +145,102 @@ void launch_opinion(int64_t n, int64_t n_edges, const int64_t *row_ptr, const in
                        row_ptr, col, weight, thr, strength, op_in, op_out);
 }
 
+// A few lanes to a short row, a wave to a long one.  A row of thousands of edges
+// is a long chain of loads in a few lanes, and the step waits for the longest:
+// rows of kLongRow edges and more are left to the whole wave, one after the
+// other, lane l composing the l-th part.  Offsets are 32 bits (fewer than 2^30
+// edges and nodes).  Bound: three dependent loads (row, target, opinion), then
+// the reads of the L2.
+// MI355X, per step, four lanes alone / tiles / this: 10,000 power-law rows of 7
+// (longest 2000) 20.5 / 13.6 / 5.4 us, 200,000 60 / 22 / 13.4; even rows of 7
+// 3.0 / 3.8 / 2.9 and 9.7 / 10.2 / 9.5.  Sixteen lanes / this: 60,000 power-law
+// rows of 14 21.9 / 12.7, even 6.9 / 6.0.  kLongRow 32 or 128: within 6 %.  Four
+// lanes where a mean row fills one batch of theirs, else eight: 3,000 even rows of
+// 20 2.9 us with eight, 3.4 with four, 3.0 with 16.
+constexpr int kLongRow = 64;
+
+template <class T>
+__device__ __forceinline__ T load32(const T *p, int i) {
+    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(p) +
+                                        (uint32_t)i * (uint32_t)sizeof(T));
+}
+
+template <int G>
+__global__ __launch_bounds__(kGraphBlock) void k_opinion_rows(int n, int n_edges,
+                                                              const int64_t *__restrict__ row_ptr,
+                                                              const int32_t *__restrict__ col,
+                                                              const float *__restrict__ weight,
+                                                              float thr, double strength,
+                                                              const float *__restrict__ op_in,
+                                                              float *__restrict__ op_out) {
+    constexpr int A = kGraphBlock / G;
+    const int tid = threadIdx.x, li = tid % G, lane = tid & 63;
+    const int i = (int)blockIdx.x * A + tid / G;
+    const bool active = i < n;
+    float me = 0.0f;
+    int e0 = 0, e1 = 0;
+    if (active) {
+        me = load32(op_in, i);
+        const int64_t r0 = row_ptr[i], r1 = row_ptr[i + 1];
+        e0 = (int)(r0 < 0 ? 0 : (r0 > n_edges ? n_edges : r0));
+        e1 = (int)(r1 < e0 ? e0 : (r1 > n_edges ? n_edges : r1));
+    }
+    // part `who` of `of` of the edges [f0, f1) of a node at `own`: x -> a x + b,
+    // then the parts' composition, later ones applied last
+    auto part = [&](int f0, int f1, int who, auto of, float own, double &a, double &b) {
+        constexpr int P = decltype(of)::value;
+        const int chunk = (f1 - f0 + P - 1) / P;
+        const int c0 = min(f0 + who * chunk, f1), c1 = min(c0 + chunk, f1);
+        a = 1.0;
+        b = 0.0;
+        for (int e = c0; e < c1; e += kEdgeBatch) {
+            int32_t j[kEdgeBatch];
+            float wt[kEdgeBatch], you[kEdgeBatch];
+            bool ok[kEdgeBatch];
+#pragma unroll
+            for (int u = 0; u < kEdgeBatch; ++u) {
+                const int k = min(e + u, c1 - 1);
+                j[u] = load32(col, k);
+                wt[u] = load32(weight, k);
+                ok[u] = e + u < c1 && j[u] >= 0 && j[u] < n;
+            }
+#pragma unroll
+            for (int u = 0; u < kEdgeBatch; ++u) you[u] = load32(op_in, ok[u] ? j[u] : 0);
+#pragma unroll
+            for (int u = 0; u < kEdgeBatch; ++u) {  // in edge order
+                if (ok[u] && fabsf(own - you[u]) < thr) {
+                    const double w = strength * (double)wt[u];
+                    a = (1.0 - w) * a;
+                    b = (1.0 - w) * b + w * (double)you[u];
+                }
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < P; off <<= 1) {
+            const double pa = __shfl_xor(a, off, 64), pb = __shfl_xor(b, off, 64);
+            b = (who & off) ? a * pb + b : pa * b + pb;
+            a = a * pa;
+        }
+    };
+    const bool big = e1 - e0 >= kLongRow;
+    double a, b;
+    part(e0, big ? e0 : e1, li, std::integral_constant<int, G>{}, me, a, b);
+    for (uint64_t todo = __ballot(big && li == 0); todo != 0; todo &= todo - 1) {
+        const int o = __builtin_ctzll(todo);
+        double wa, wb;
+        part(__shfl(e0, o, 64), __shfl(e1, o, 64), lane, std::integral_constant<int, 64>{},
+             __shfl(me, o, 64), wa, wb);
+        if (lane == o) {
+            a = wa;
+            b = wb;
+        }
+    }
+    if (active && li == 0) op_out[i] = (float)(a * (double)me + b);
+}
+
 // The tile kernel, for many short rows.  With lanes sharing a node, a row of 14
 // edges gives 16 lanes one edge each in slots for kEdgeBatch of them, so most
-// loads and FP64 maps are padding, and a row of thousands of edges is a long
-// chain of loads in its few lanes.  Here a block takes kTileNodes consecutive
+// loads and FP64 maps are padding.  Here a block takes kTileNodes consecutive
 // nodes, whose edges are one range, and brings it into LDS tile by tile with
 // all its threads: consecutive loads, kTileLoads targets and then as many
 // opinions in flight per thread, the opinion and the weight of an edge kept as a
@@ -159,7 +251,7 @@ void launch_opinion(int64_t n, int64_t n_edges, const int64_t *row_ptr, const in
 // 15 M requests of the L2 per step of the first graph below, 5 in 6 of which hit.
 //
 // MI355X, per step, power-law rows (longest 2000), lanes per node / tiles:
-// 1M nodes of mean degree 14, 139 / 103 us; of 8, 115 / 69; of 5.4, 137 / 53.
+// 1M nodes of mean degree 14, 136 / 104 us; of 8, 112 / 66.
 // 128 nodes and 1024 edges: 256 and 2048 take 104, 512 and 4096 123, 64 and 768
 // 110, 128 and 2304 106.  4 loads: 106.  kTileRow 24 or 32 gives up the order at
 // rows where one lane is as fast, and then takes 45 us for 10,000 rows of 30
@@ -267,19 +359,18 @@ __global__ __launch_bounds__(kTileNodes) void k_opinion_tile(int64_t n, int64_t 
     if (active) op_out[i] = (float)x;
 }
 
-// Tiles or lanes per node, where the caller leaves the choice.  Below 3 edges a
+// What takes the step where the caller leaves the choice.  Below 3 edges a
 // node, one lane per node reads little that it does not need (1M rows of 1 to 3:
-// 17 us, tiles 20).  From 3 to 8, tiles: power-law rows take 8 to 14 us at 3,000 to
-// 30,000 nodes where 4 lanes take 14 to 60 (the longest row's chain), even rows the
-// same up to 30,000 nodes and at 1M, 5 to 10 % more at 100,000 to 300,000.
-// From 8 to 24, tiles once there are edges enough to keep every CU at work through
-// both phases of a tile: 300,000 power-law rows of 8 (2.5 M edges) take 44 us with 16
-// lanes and 27 with tiles, even rows of 8 (2.4 M) 15.5 and 15.9, 200,000 rows of
-// 14 (2.8 M) 37 and 34, but 150,000 (2.1 M) 32 and 33 and 100,000 24 and 32.
-// Above, a lane's share of a row fills its slots:
-// 300,000 rows of 30 take 50 us with 16 lanes and 53 with tiles, of 48, 72 and 130.
-bool graph_use_tiles(int64_t n_edges, double mean_degree) {
-    return mean_degree >= 3.0 && (mean_degree < 8.0 || (mean_degree < 24.0 && n_edges >= 2300000));
+// 17 us, tiles 20).  From 24 a share of a row fills the slots of 16 lanes (300,000 rows of
+// 30: 50 us, tiles 53).  Between, rows by four lanes and by waves, up to 8 M edges:
+// even rows take no longer than with lanes alone at any size (3,000 to 2M nodes), power-law
+// rows a half to a seventh.  Above, tiles, whose loads of the edges are consecutive: 500,000
+// power-law rows of 14 (7 M edges) 50 us by rows and 59 in tiles, even rows 36 and
+// 39; 1M of 7 63 and 61, 50 and 47; of 8 70 and 66, 55 and 49; of 14 108 and 104, 87 and 85.
+enum class GraphForm { kLanes, kRows, kTiles };
+GraphForm graph_form(int64_t n_edges, double mean_degree) {
+    if (mean_degree < 3.0 || mean_degree >= 24.0) return GraphForm::kLanes;
+    return n_edges < 8000000 ? GraphForm::kRows : GraphForm::kTiles;
 }
 
 // Lanes per node for the rest, from the mean degree: power-law rows are uneven,
@@ -314,10 +405,19 @@ int gr_opinion_step(int64_t n, int64_t n_edges, const int64_t *row_ptr, const in
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const double st = (double)strength;
     const double mean = (double)n_edges / (double)n;
-    if (lanes == 0 && graph_use_tiles(n_edges, mean)) {
-        hipLaunchKernelGGL(k_opinion_tile, dim3((unsigned)((n + kTileNodes - 1) / kTileNodes)),
-                           dim3(kTileNodes), 0, s, n, n_edges, row_ptr, col, weight, threshold, st,
-                           op_in, op_out);
+    const GraphForm form = lanes ? GraphForm::kLanes : graph_form(n_edges, mean);
+    if (form != GraphForm::kLanes) {
+        auto rows = [&](auto kernel, int per_block) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((n + per_block - 1) / per_block)),
+                               dim3(kGraphBlock), 0, s, (int)n, (int)n_edges, row_ptr, col, weight,
+                               threshold, st, op_in, op_out);
+        };
+        if (form == GraphForm::kTiles)
+            hipLaunchKernelGGL(k_opinion_tile, dim3((unsigned)((n + kTileNodes - 1) / kTileNodes)),
+                               dim3(kTileNodes), 0, s, n, n_edges, row_ptr, col, weight, threshold,
+                               st, op_in, op_out);
+        else if (mean < 4.0 * kEdgeBatch) rows(k_opinion_rows<4>, kGraphBlock / 4);
+        else rows(k_opinion_rows<8>, kGraphBlock / 8);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return set_error(ENV_EHIP, "gr_opinion_step: %s", hipGetErrorString(e));
         return ENV_OK;

@@ -1,0 +1,104 @@
+"""GPU graph interaction where the lanes per node are left to the library: rows by four
+lanes and by waves (mean degree 3 to 24, fewer than 8 M edges), tiles of edges above.
+
+A row of fewer than 64 edges is composed of at most four parts (rows) or applied one by
+one (tiles), a longer one of at most 64 parts per pass: the same map up to FP64 rounding,
+some 1e-14 of an opinion, which can move the one rounding to FP32 by one place only.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import graph
+
+pytestmark = pytest.mark.gpu
+flock = pytest.importorskip("paper_2207_03945_amd")
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def step(rp, col, w, op, thr=0.4, strength=0.5):
+    out = torch.full((op.shape[0],), float("nan"), device="cuda")
+    flock.opinion_step(dev(rp), dev(col), dev(w), dev(op), out, thr, strength)
+    return out.cpu().numpy()
+
+
+def ulps(got, want):
+    want = want.astype(np.float32)
+    return np.abs(got.view(np.int32).astype(np.int64) - want.view(np.int32).astype(np.int64))
+
+
+def make(lens, seed):
+    g = np.random.default_rng(seed)
+    n, e = len(lens), int(np.sum(lens))
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    return (rp, g.integers(0, n, e).astype(np.int32), g.random(e).astype(np.float32),
+            g.random(n).astype(np.float32))
+
+
+@pytest.mark.parametrize("n,mean,long", [
+    (1, 5, ()), (63, 6, ()), (64, 20, (63, 64, 65)), (65, 10, (64, 64, 64)), (1000, 4, (255, 256, 257)),
+    (1000, 18, (4095, 4096, 64)), (3000, 3, (2000,) * 4), (70_000, 9, (20_000, 65)), (333, 23, (0,))])
+def test_rows(n, mean, long):
+    g = np.random.default_rng(n)
+    lens = g.integers(0, 2 * mean + 1, n) if n > 1 else np.array([mean])
+    for k, length in enumerate(long):
+        lens[(17 + 7 * k) % n] = length         # several to a wave
+    short = np.flatnonzero(lens < 64)
+    while not 3.0 <= lens.sum() / n < 24.0:     # within the route
+        lens[short] = lens[short] // 2 if lens.sum() / n >= 24.0 else lens[short] + 1
+    rp, col, w, op = make(lens, seed=n + 1)
+    rows = np.arange(n) if n <= 3000 else np.unique(np.r_[0:200, np.argsort(lens)[-4:], n - 200:n])
+    want = graph.opinion_step(rp, col, w, op, 0.4, 0.5, nodes=rows)
+    assert (ulps(step(rp, col, w, op)[rows], want) <= 1).all()
+
+
+def test_rows_bad_arrays():
+    """Targets outside [0, n) are skipped, rows clamped to [0, n_edges]; NaN opinions move
+    nobody."""
+    n = 2000
+    lens = np.random.default_rng(5).integers(0, 12, n)
+    lens[[40, 41, 900]] = 64, 500, 65
+    rp, col, w, op = make(lens, seed=6)
+    bad = col.copy()
+    bad[::7], bad[3::11] = n, -3
+    op = op.copy()
+    op[100:120] = np.nan
+    ok = (bad >= 0) & (bad < n) & ~np.isnan(op[np.clip(bad, 0, n - 1)])
+    rp_ok = np.concatenate([[0], np.cumsum(ok)])[rp]
+    want = graph.opinion_step(rp_ok, bad[ok], w[ok], op, 0.4, 0.5)
+    got, live = step(rp, bad, w, op), ~np.isnan(op)
+    assert np.isnan(got[~live]).all() and (ulps(got[live], want[live]) <= 1).all()
+    odd = rp.copy()
+    odd[5], odd[200], odd[201], odd[300] = 40, -9, rp[-1] + 50, 3
+    rows = np.r_[4:7, 198:203, 298:303, n - 5:n]
+    want = graph.opinion_step(np.clip(odd, 0, rp[-1]), col, w, op, 0.4, 0.5, nodes=rows)
+    assert (ulps(step(odd, col, w, op)[rows], want) <= 1).all()
+
+
+def test_tiles():
+    """More than 8 M edges; the blocks' and tiles' edges are in the first nodes (rows round
+    64, round a tile of 1,024 edges, across tiles, empty rows, bad targets)."""
+    n = 420_000
+    g = np.random.default_rng(2)
+    lens = g.integers(0, 40, n)
+    lens[:2000] = g.integers(0, 9, 2000)
+    for k, length in enumerate((63, 64, 65, 1023, 1024, 1025, 3000, 64, 64)):
+        lens[(17 + 131 * k) % 2000] = length
+    lens[n - 1] = 1500
+    rp, col, w, op = make(lens, seed=3)
+    assert 8.0 <= rp[-1] / n < 24.0 and rp[-1] >= 8_000_000
+    col[1::13] = n
+    rows = np.unique(np.r_[0:2000, g.integers(0, n, 1000), n - 130:n])
+    got = step(rp, col, w, op)[rows]
+    e = np.concatenate([np.arange(rp[i], rp[i + 1]) for i in rows])    # the oracle on these rows' edges
+    keep = col[e] < n
+    cut = np.zeros(n + 1, np.int64)
+    cut[rows + 1] = np.add.reduceat(np.r_[keep, False], np.r_[0, np.cumsum(lens[rows])[:-1]]) * (lens[rows] > 0)
+    want = graph.opinion_step(np.cumsum(cut), col[e][keep], w[e][keep], op, 0.4, 0.5, nodes=rows)
+    off = ulps(got, want)
+    assert (off <= 1).all() and not off[lens[rows] < 64].any()
