@@ -41,6 +41,7 @@
 #include <limits.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 
 #include <type_traits>
@@ -2102,11 +2103,21 @@ int strip_cols_for(const DevEnv &d, int64_t G) {
     return std::min(cols, d.ncx);
 }
 
-void plan_strip_device(StepPlan *p) {
+// CUs of the current device (asked for once per device).
+static int device_cus() {
+    static std::atomic<int> known[64];
     int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    cus = known[dev].load(std::memory_order_relaxed);
+    if (cus > 0) return cus;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        return 256;
+    known[dev].store(cus, std::memory_order_relaxed);
+    return cus;
+}
+
+void plan_strip_device(StepPlan *p) {
+    const int cus = device_cus();
     p->strips_wide = strips_wide(p->strips, cus);
     p->strips_ahead = strips_ahead(p->strips, p->n_envs, p->strips_per_cu * cus);
 }
