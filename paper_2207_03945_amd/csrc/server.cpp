@@ -100,6 +100,14 @@ namespace {
 // Retired requests' returns come down through this much page-locked memory at a
 // time (1 MiB), several requests to one wait.
 constexpr size_t kPinnedReturns = (1u << 20) / sizeof(double);
+
+// While it lives, this thread may take and give back page-locked memory though
+// some stream of the process is captured (which such a call would invalidate).
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
 }  // namespace
 
 struct flock_server {
@@ -231,6 +239,7 @@ int try_admit(srv_t *S, Request &r) {
 hipError_t download_returns(srv_t *S, const std::vector<Request *> &reqs) {
     if (!S->pinned) {  // at the first retirement: a tick waits for its stream anyway
         void *pin = nullptr;
+        RelaxedCapture relaxed;
         if (hipHostMalloc(&pin, kPinnedReturns * sizeof(double), hipHostMallocDefault) == hipSuccess)
             S->pinned = static_cast<double *>(pin);
         else
@@ -401,7 +410,10 @@ void srv_destroy(srv_t *S) {
     if (!S) return;
     for (auto &kv : S->reqs)
         if (kv.second.env) env_destroy(kv.second.env);
-    if (S->pinned) (void)hipHostFree(S->pinned);
+    if (S->pinned) {
+        RelaxedCapture relaxed;
+        (void)hipHostFree(S->pinned);
+    }
     delete S;
 }
 
