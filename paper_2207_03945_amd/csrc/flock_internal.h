@@ -121,6 +121,8 @@ struct StepPlan {
     int env_sort_recs;      // > 0: one block per env does move to scatter (records per thread)
     int strips;             // > 0: the envs' column strips (the strip sort is allowed)
     int strips_wide = 0;    // blocks of 1,024 threads (strip_order.h)
+    int strips_most = 1;    // strips of the env that has most
+    int strip_run_log = -1; // the launch order's runs (strip_order.h)
     int strips_ahead = 0;   // envs' first strips at the head of the launch (strip_order.h)
     int strip_now;          // this launch may use the strip sort (every env's records sorted)
     int strip_cells;        // cells of the plan's largest strip
@@ -196,7 +198,7 @@ int64_t assign_strips(DevEnv *const *tabs, int n_tabs, int n_envs, int64_t G,
 void plan_strip_device(StepPlan *p);
 // The same, returning the env of each strip in launch order, the plan's strip_env.
 std::vector<int32_t> strip_launch_order(StepPlan *p, const std::vector<int32_t> &strips_of);
-// Fill the plan's strip_cells and strip_cap from its envs' descriptors (after assign_strips).
+// Fill the plan's strip_cells, strips_most and strip_cap from its envs' descriptors (after assign_strips).
 void plan_strip_launch(StepPlan *p, const DevEnv *envs, int n_envs);
 
 // Launchers (return hipSuccess or the first error) ------------------------

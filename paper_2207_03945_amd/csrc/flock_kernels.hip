@@ -686,17 +686,18 @@ __device__ int strip_base_by_count(const DevEnv &E, int c0, int do_move,
     return cnt;
 }
 
-template <int NT, int R, int kWaves, bool kAhead, bool kList>
+template <int NT, int R, int kWaves, bool kOrdered, bool kList>
 __global__ __launch_bounds__(NT, kWaves) void k_strip_sort(
     SortArrays a, const DevEnv *__restrict__ envs, int n_envs, int C, int G, int S, int do_move,
-    const float2 *__restrict__ act, int tag, float2 *__restrict__ act_copy, int run_len, int wait, int cap) {
+    const float2 *__restrict__ act, int tag, float2 *__restrict__ act_copy, int n_ahead,
+    int run_len, int run_log, int wait, int cap) {
     // the strip's cells: counts, then each cell's first row; then the list
     extern __shared__ int s_cells[];
     __shared__ int s_wave[NT / 64 + 1], s_probe[NT / 64];
     __shared__ int s_base, s_side, s_listed;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int ahead = kAhead ? n_envs : 0;
-    const int place = strip_place(blockIdx.x, ahead, run_len);
+    const int ahead = kOrdered ? n_ahead : 0;
+    const int place = strip_place(blockIdx.x, ahead, run_len, kOrdered ? run_log : -1);
     if (place >= S) return;  // a block past the last strip
     const int e = n_envs == 1 ? 0 : a.strip_env[place];
     const DevEnv &E = envs[e];
@@ -2120,6 +2121,7 @@ void plan_strip_device(StepPlan *p) {
     const int cus = device_cus();
     p->strips_wide = strips_wide(p->strips, cus);
     p->strips_ahead = strips_ahead(p->strips, p->n_envs, p->strips_per_cu * cus);
+    p->strip_run_log = strip_run_log(p->strips, p->strips_most, cus);
 }
 
 std::vector<int32_t> strip_launch_order(StepPlan *p, const std::vector<int32_t> &strips_of) {
@@ -2132,9 +2134,13 @@ std::vector<int32_t> strip_launch_order(StepPlan *p, const std::vector<int32_t> 
 }
 
 void plan_strip_launch(StepPlan *p, const DevEnv *envs, int n_envs) {
-    int cells = 1;
-    for (int e = 0; e < n_envs; ++e) cells = std::max(cells, envs[e].strip_cols * envs[e].ncy);
+    int cells = 1, most = 1;
+    for (int e = 0; e < n_envs; ++e) {
+        cells = std::max(cells, envs[e].strip_cols * envs[e].ncy);
+        most = std::max(most, envs[e].n_strips);
+    }
     p->strip_cells = cells;
+    p->strips_most = most;
     // Strips whose neighbouring columns alone exceed the registers list their
     // agents beyond them (uniform agents' and four deviations), in the LDS that
     // leaves a CU four, three or two blocks.  Where less is read again, reading it
@@ -2275,18 +2281,19 @@ hipError_t launch_phase(const StepPlan &p, int table, StepPhase phase, int do_mo
             if (p.env_sort_recs == 0 && p.strips > 0 && p.strip_now) {
                 auto go = [&](auto kernel, int nt, int cap) {
                     const size_t lds = (((p.strip_cells + 3) & ~3) + 4 * (size_t)cap) * sizeof(int);
-                    hipLaunchKernelGGL(kernel, dim3(strip_blocks(p.strips, p.strips_ahead)), dim3(nt),
+                    hipLaunchKernelGGL(kernel, dim3(strip_blocks(p.strips, p.strips_ahead, p.strip_run_log)), dim3(nt),
                                        lds, s, p.a, envs, p.n_envs, C, G, (int)p.strips, do_move,
                                        reinterpret_cast<const float2 *>(act), p.tag,
                                        reinterpret_cast<float2 *>(act_copy),
-                                       (int)strip_run(p.strips, p.strips_ahead), p.strip_wait, cap);
+                                       p.strips_ahead, (int)strip_run(p.strips, p.strips_ahead), p.strip_run_log,
+                                       p.strip_wait, cap);
                 };
                 // one block per CU: latency; more: see the kernel
-                const bool ahead = p.strips_ahead > 0;
+                const bool ordered = p.strips_ahead > 0 || p.strip_run_log >= 0;
                 const int cap = p.strip_cap;
-                if (p.strips_wide && !ahead) go(k_strip_sort<1024, 4, 4, false, false>, 1024, 0);
-                else if (ahead && cap) go(k_strip_sort<512, 3, 8, true, true>, 512, cap);
-                else if (ahead) go(k_strip_sort<512, 3, 8, true, false>, 512, 0);
+                if (p.strips_wide && !ordered) go(k_strip_sort<1024, 4, 4, false, false>, 1024, 0);
+                else if (ordered && cap) go(k_strip_sort<512, 3, 8, true, true>, 512, cap);
+                else if (ordered) go(k_strip_sort<512, 3, 8, true, false>, 512, 0);
                 else if (cap) go(k_strip_sort<512, 3, 8, false, true>, 512, cap);
                 else go(k_strip_sort<512, 3, 8, false, false>, 512, 0);
                 break;

@@ -21,3 +21,11 @@ WIDE = 8192.0
 @pytest.mark.parametrize("kind", ["edge", "uniform"])
 def test_more_strips_than_are_resident(sizes, kind):
     strip_equals_general(sizes, kind)
+
+
+@pytest.mark.parametrize("kind", ["edge", "dense"])
+def test_short_runs(kind):
+    """Envs that span several XCDs, whose strips are dealt out in runs of eight: alone, and
+    beside a small one with more strips than are resident."""
+    strip_equals_general([(150_000, 1549.0)], kind)
+    strip_equals_general([(9000, 2 * WIDE), (500, 300.0)], kind)
