@@ -254,8 +254,9 @@ int env_batch_set_policy_fusion(env_batch_t *b, int on);
  * 16384).  The sort cuts each env's grid columns into strips, one block each,
  * and a strip takes its first output row from its own records and from the
  * count of agents that crossed the box's edge, which the env's first strip
- * publishes; a strip whose wait runs out counts the agents before it itself.  Results are the same for every value: 0 makes every such strip count
- * (the fallback, for tests).  Drops captured graphs when the value changes.
+ * publishes (its first and last strip need no count); a strip whose wait runs
+ * out counts the agents before it itself.  Results are the same for every
+ * value: 0 makes every such strip count (the fallback, for tests).  Drops captured graphs when the value changes.
  * ENV_EINVAL for a NULL batch or polls < 0. */
 int env_batch_set_strip_wait(env_batch_t *b, int polls);
 
@@ -406,10 +407,10 @@ int env_step_policy(env_batch_t *b, pol_t *pol, float *act, float *obs, float *r
  *   op_in, op_out  device FP32 [n], distinct
  * Updates run in FP64, rounded once to FP32.  lanes: lanes per node (1, 4,
  * 16, 64; 0 = from the mean degree and the number of edges, where long rows
- * may be taken by whole waves and short ones in blocks).  With lanes = 1 each node applies its edges one by
- * one in the stated order; otherwise parts of the row may be composed as
- * affine maps (the same map up to FP64 rounding).  0 <= n <
- * 2^31.  ENV_EINVAL on bad sizes, NULL arrays, op_in == op_out. */
+ * may be taken by whole waves and short ones in blocks).  With lanes = 1 each
+ * node applies its edges one by one in the stated order; otherwise parts of the
+ * row may be composed as affine maps (the same map up to FP64 rounding).
+ * 0 <= n < 2^31.  ENV_EINVAL on bad sizes, NULL arrays, op_in == op_out. */
 int gr_opinion_step(int64_t n, int64_t n_edges, const int64_t *row_ptr, const int32_t *col,
                     const float *weight, float threshold, float strength, const float *op_in,
                     float *op_out, int lanes, void *stream);
@@ -426,6 +427,11 @@ int gr_opinion_step(int64_t n, int64_t n_edges, const int64_t *row_ptr, const in
  * run at once.  All requests share `pol`: their view row length d must
  * equal pol's in, and every request has the sector count of the first one
  * submitted (ENV_EINVAL otherwise).  Fields of view may differ.
+ * Host memory: queued and running requests hold their initial state, finished
+ * ones their returns, and the tick that first retires a request takes 1 MiB of
+ * page-locked memory for returns to come down through (15 to 200 us, once per
+ * server), which srv_destroy gives back; where that is refused, returns come
+ * down to pageable memory.
  */
 int srv_create(void *arena, size_t arena_bytes, int max_slots, pol_t *pol,
                void *stream, srv_t **out);

@@ -63,28 +63,11 @@ __device__ __forceinline__ int cell_of(float v, float inv, int ncell) {
     return c > 0 ? c : 0;
 }
 
-// Last env e with base[e] <= row (skips empty envs, whose base equals the next).
-__device__ __forceinline__ int env_search(const int32_t *base, int n_envs, int row) {
-    int lo = 0, hi = n_envs - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (base[mid] <= row) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
-constexpr bool kWaveSearch = true;
-
 // Env of the block's first row into s_env (wave 0 searches).
 __device__ __forceinline__ void block_env(int *s_env, const int32_t *base, int n_envs, int row) {
-    if (kWaveSearch) {
-        if (threadIdx.x < 64) {
-            const int e = wave_env_search(base, n_envs, row);
-            if (threadIdx.x == 0) *s_env = e;
-        }
-    } else if (threadIdx.x == 0) {
-        *s_env = env_search(base, n_envs, row);
+    if (threadIdx.x < 64) {
+        const int e = wave_env_search(base, n_envs, row);
+        if (threadIdx.x == 0) *s_env = e;
     }
 }
 

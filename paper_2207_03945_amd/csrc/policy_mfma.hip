@@ -231,13 +231,6 @@ uint16_t bf16_bits_rne(float f) {
     return (uint16_t)(u >> 16);
 }
 
-float bf16_round(float f) {
-    uint32_t u = (uint32_t)bf16_bits_rne(f) << 16;
-    float r;
-    memcpy(&r, &u, 4);
-    return r;
-}
-
 }  // namespace
 
 }  // namespace flock

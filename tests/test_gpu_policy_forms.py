@@ -69,3 +69,16 @@ def test_tag_rollout(n, sampled):
         else:
             a = pol.forward(part)
         assert torch.equal(a, act[0, lo:hi]), (lo, hi)
+
+
+@pytest.mark.parametrize("d", [1, 7, 8, 9, 17, 33, 128, 129, 250, 256, 257])
+def test_rows_of_any_alignment(d):
+    """Rows that start on any four bytes, the last of them at the end of its buffer."""
+    pol = flock.Policy(*workloads.xavier_weights([d, 64, 64, 2], seed=d))
+    n = 333
+    want = pol.forward(views(n, d, d))
+    for off in (1, 2, 3):
+        flat = torch.empty(off + n * d, device="cuda")
+        rows = flat[off:].view(n, d)
+        rows.copy_(views(n, d, d))
+        assert torch.equal(pol.forward(rows), want), off
