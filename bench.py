@@ -45,7 +45,10 @@ HBM_PEAK = 8.0e12          # MI355X HBM3E, bytes/s
 # clock (157.3 TFLOP/s counts an FMA as 2 and packed FP32 as 2 more; packed
 # FP32 is not generated here).
 VALU_PEAK = 256 * 64 * 2.4e9
-VALU_ISSUE_PEAK = 256 * 2.4e9   # wave64 VALU instructions per second (one per clock per CU)
+# Wave64 VALU instructions per second: a CU issues 1.7 per clock of the simple FP32
+# and integer kinds (measured with independent ones), about half as many of compares,
+# selects, minima, conversions and those with a scalar operand.
+VALU_ISSUE_PEAK = 256 * 1.7 * 2.4e9
 OPS_PER_CANDIDATE = 12     # image shift, d^2, radius and self tests, counts
 OPS_PER_NEIGHBOUR = 30     # bearing, sector, per-sector minimum
 V = 16                     # sectors of the paper-scale workloads
