@@ -152,11 +152,13 @@ void launch_opinion(int64_t n, int64_t n_edges, const int64_t *row_ptr, const in
 // edges and nodes).  Bound: three dependent loads (row, target, opinion), then
 // the reads of the L2.
 // MI355X, per step, four lanes alone / tiles / this: 10,000 power-law rows of 7
-// (longest 2000) 20.5 / 13.6 / 5.4 us, 200,000 60 / 22 / 13.4; even rows of 7
-// 3.0 / 3.8 / 2.9 and 9.7 / 10.2 / 9.5.  Sixteen lanes / this: 60,000 power-law
-// rows of 14 21.9 / 12.7, even 6.9 / 6.0.  kLongRow 32 or 128: within 6 %.  Four
-// lanes where a mean row fills one batch of theirs, else eight: 3,000 even rows of
-// 20 2.9 us with eight, 3.4 with four, 3.0 with 16.
+// (longest 2000) 20.6 / 13.7 / 7.0 us, 200,000 60 / 22 / 15.3; even rows of 7
+// 3.0 / 3.8 / 2.9 and 9.7 / 10.0 / 9.0, with near targets 2.8 / 3.7 / 2.8 and
+// 7.3 / 5.0 / 5.1.  Sixteen lanes / this: 60,000 power-law rows of 14 21.9 / 12.7,
+// even 6.9 / 6.0.  kLongRow 32 or 128: within 6 %.  As many lanes as a mean row
+// fills one batch of: two up to 8 edges (four take 5.5 and 13.7 us for the power-law
+// rows of 7, but 2.9 and 9.5 for the even ones and 2.8 and 7.0 for the near ones),
+// four up to 16, else eight (3,000 even rows of 20 2.9 us, with four 3.4, with 16 3.0).
 constexpr int kLongRow = 64;
 
 template <class T>
@@ -362,15 +364,16 @@ __global__ __launch_bounds__(kTileNodes) void k_opinion_tile(int64_t n, int64_t 
 // What takes the step where the caller leaves the choice.  Below 3 edges a
 // node, one lane per node reads little that it does not need (1M rows of 1 to 3:
 // 17 us, tiles 20).  From 24 a share of a row fills the slots of 16 lanes (300,000 rows of
-// 30: 50 us, tiles 53).  Between, rows by four lanes and by waves, up to 8 M edges:
-// even rows take no longer than with lanes alone at any size (3,000 to 2M nodes), power-law
-// rows a half to a seventh.  Above, tiles, whose loads of the edges are consecutive: 500,000
-// power-law rows of 14 (7 M edges) 50 us by rows and 59 in tiles, even rows 36 and
-// 39; 1M of 7 63 and 61, 50 and 47; of 8 70 and 66, 55 and 49; of 14 108 and 104, 87 and 85.
+// 30: 50 us, tiles 53).  Between, rows by a few lanes and by waves: even rows take no
+// longer than with lanes alone at any size (3,000 to 2M nodes), power-law
+// rows a half to a seventh.  In large graphs tiles, whose loads of the edges are
+// consecutive: power-law / even rows of 5 at 1M nodes (5.2 and 5.0 M edges) 52 / 35 us by
+// rows and 47 / 38 in tiles, of 7 68 / 46 and 63 / 47; longer rows from 8 M edges: 500,000 of
+// 14 (7 M) 50 / 36 and 59 / 39, 1M of 8 70 / 55 and 66 / 49, of 14 108 / 87 and 104 / 85.
 enum class GraphForm { kLanes, kRows, kTiles };
 GraphForm graph_form(int64_t n_edges, double mean_degree) {
     if (mean_degree < 3.0 || mean_degree >= 24.0) return GraphForm::kLanes;
-    return n_edges < 8000000 ? GraphForm::kRows : GraphForm::kTiles;
+    return n_edges < (mean_degree <= 8.0 ? 5000000 : 8000000) ? GraphForm::kRows : GraphForm::kTiles;
 }
 
 // Lanes per node for the rest, from the mean degree: power-law rows are uneven,
@@ -416,6 +419,7 @@ int gr_opinion_step(int64_t n, int64_t n_edges, const int64_t *row_ptr, const in
             hipLaunchKernelGGL(k_opinion_tile, dim3((unsigned)((n + kTileNodes - 1) / kTileNodes)),
                                dim3(kTileNodes), 0, s, n, n_edges, row_ptr, col, weight, threshold,
                                st, op_in, op_out);
+        else if (mean <= 2.0 * kEdgeBatch) rows(k_opinion_rows<2>, kGraphBlock / 2);
         else if (mean < 4.0 * kEdgeBatch) rows(k_opinion_rows<4>, kGraphBlock / 4);
         else rows(k_opinion_rows<8>, kGraphBlock / 8);
         const hipError_t e = hipGetLastError();

@@ -1,7 +1,7 @@
-"""GPU graph interaction where the lanes per node are left to the library: rows by four
-lanes and by waves (mean degree 3 to 24, fewer than 8 M edges), tiles of edges above.
+"""GPU graph interaction where the lanes per node are left to the library: rows by two
+to eight lanes and by waves (mean degree 3 to 24, fewer than 8 M edges, 5 M where the mean is up to 8), tiles above.
 
-A row of fewer than 64 edges is composed of at most four parts (rows) or applied one by
+A row of fewer than 64 edges is composed of at most eight parts (rows) or applied one by
 one (tiles), a longer one of at most 64 parts per pass: the same map up to FP64 rounding,
 some 1e-14 of an opinion, which can move the one rounding to FP32 by one place only.
 """
@@ -41,7 +41,8 @@ def make(lens, seed):
 
 
 @pytest.mark.parametrize("n,mean,long", [
-    (1, 5, ()), (63, 6, ()), (64, 20, (63, 64, 65)), (65, 10, (64, 64, 64)), (1000, 4, (255, 256, 257)),
+    (1, 5, ()), (1, 8, ()), (1, 9, ()), (1, 16, ()), (63, 6, ()), (127, 8, (64,)), (129, 7, (63, 64)),
+    (64, 20, (63, 64, 65)), (65, 10, (64, 64, 64)), (1000, 4, (255, 256, 257)),
     (1000, 18, (4095, 4096, 64)), (3000, 3, (2000,) * 4), (70_000, 9, (20_000, 65)), (333, 23, (0,))])
 def test_rows(n, mean, long):
     g = np.random.default_rng(n)
@@ -80,18 +81,18 @@ def test_rows_bad_arrays():
     assert (ulps(step(odd, col, w, op)[rows], want) <= 1).all()
 
 
-def test_tiles():
-    """More than 8 M edges; the blocks' and tiles' edges are in the first nodes (rows round
+@pytest.mark.parametrize("n,most,edges", [(420_000, 40, 8_000_000), (1_000_000, 12, 5_000_000)])
+def test_tiles(n, most, edges):
+    """More than 8 M edges, 5 M of short rows; the blocks' and tiles' edges are in the first nodes (rows round
     64, round a tile of 1,024 edges, across tiles, empty rows, bad targets)."""
-    n = 420_000
     g = np.random.default_rng(2)
-    lens = g.integers(0, 40, n)
+    lens = g.integers(0, most, n)
     lens[:2000] = g.integers(0, 9, 2000)
     for k, length in enumerate((63, 64, 65, 1023, 1024, 1025, 3000, 64, 64)):
         lens[(17 + 131 * k) % 2000] = length
     lens[n - 1] = 1500
     rp, col, w, op = make(lens, seed=3)
-    assert 8.0 <= rp[-1] / n < 24.0 and rp[-1] >= 8_000_000
+    assert (3.0 if most < 16 else 8.1) <= rp[-1] / n < (8.0 if most < 16 else 24.0) and rp[-1] >= edges
     col[1::13] = n
     rows = np.unique(np.r_[0:2000, g.integers(0, n, 1000), n - 130:n])
     got = step(rp, col, w, op)[rows]
